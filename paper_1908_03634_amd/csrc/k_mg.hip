@@ -1,9 +1,8 @@
 // k_mg.hip -- gfx950 multigrid kernels launched one per operation: one colour
 // of red-black Gauss-Seidel (the reference the fused sweep is checked
 // against, and the fallback for odd periodic extents), residual + 8-cell
-// restriction, piecewise-constant prolongation, the workgroup BiCGStab
-// bottom solve for coarsest grids too large for one wavefront, and the FP64
-// finest-level operator, residual and update of the iterative refinement.
+// restriction, piecewise-constant prolongation, and the FP64 finest-level
+// operator, residual and update of the iterative refinement.
 //
 // The stencils are bandwidth-bound (about 20 flops per 24-48 bytes), so no
 // matrix cores are involved.  Launches are 3D (x fastest, 64 lanes along x)
@@ -297,225 +296,6 @@ void launch_prolong(const Dims& fine, T* phi, const T* coarse_phi, hipStream_t s
     hipLaunchKernelGGL((k_prolong<T>), sh.grid, sh.block, 0, s, fine, phi, coarse_phi);
 }
 
-// ------------------------------------------------------------ bottom solve
-
-// Block minimum; every thread receives the same value (sh as for block_sum).
-__device__ __forceinline__ double block_min(double v, double* sh)
-{
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v = fmin(v, __shfl_xor(v, o, kWave));
-    const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave, nw = (blockDim.x + kWave - 1) / kWave;
-    __syncthreads();
-    if (lane == 0) sh[w] = v;
-    __syncthreads();
-    double m = sh[0];
-    for (int i = 1; i < nw; i++) m = fmin(m, sh[i]);
-    return m;
-}
-
-// The six face coefficients of cell q (stencil order), FP64.
-template <typename T>
-__device__ __forceinline__ void face6(const T* cx, const T* cy, const T* cz, long long q, const Nbr& nb, double (&c)[6])
-{
-    c[0] = (double)cx[q];
-    c[1] = (double)ld_or0(cx, nb.cxp);
-    c[2] = (double)cy[q];
-    c[3] = (double)ld_or0(cy, nb.cyp);
-    c[4] = (double)cz[q];
-    c[5] = (double)ld_or0(cz, nb.czp);
-}
-
-// BiCGStab in FP64 for A x = b on the coarsest grid, run by one workgroup
-// (used when that grid holds more cells than one wavefront solves in
-// registers).  The constants on each connected part of the grid (cells
-// joined through nonzero faces) span the null space, so b is made mean-zero
-// part by part first and the result is returned so (with every cell coupled:
-// the plain mean removal, in the same operations).  With use_x0 the
-// iteration starts from the x passed in and stops at rtol times the initial
-// residual; otherwise it starts from zero.  An unconverged solve returns the
-// iterate of the smallest residual.  work holds 9 n doubles.
-template <typename T>
-__global__ __launch_bounds__(1024) void k_bottom(Dims d, const T* __restrict__ bin, T* __restrict__ xout,
-                                                 const T* __restrict__ cx, const T* __restrict__ cy,
-                                                 const T* __restrict__ cz, double h2, double rtol, int maxit,
-                                                 int use_x0, double* __restrict__ work, double* __restrict__ iters,
-                                                 const double* __restrict__ skip_if_direct)
-{
-    __shared__ double sh[16];
-    if (skip_if_direct && skip_if_direct[0] == 1.0) return;
-    const int n = (int)d.n();
-    const int tid = threadIdx.x, nt = blockDim.x;
-    double* x = work;
-    double* r = work + n;
-    double* rh = work + 2 * n;
-    double* p = work + 3 * n;
-    double* v = work + 4 * n;
-    double* s = work + 5 * n;
-    double* tv = work + 6 * n;
-    double* xb = work + 7 * n;
-    double* lab = work + 8 * n;  // connected-part label: smallest cell index of the part
-    const double inv_h2 = 1.0 / h2;
-
-    // labels by minimum-label propagation (in place: the fixed point, each
-    // part's smallest index, does not depend on the order of the updates)
-    for (int q = tid; q < n; q += nt) lab[q] = (double)q;
-    for (;;) {
-        __syncthreads();
-        double changed = 0.0;
-        for (int q = tid; q < n; q += nt) {
-            int i, j, k;
-            cell_ijk(d, q, i, j, k);
-            const Nbr nb = neighbours(d, q, i, j, k);
-            double c[6];
-            face6<T>(cx, cy, cz, q, nb, c);
-            const long long nq[6] = {nb.xm, nb.xp, nb.ym, nb.yp, nb.zm, nb.zp};
-            double m = lab[q];
-#pragma unroll
-            for (int f = 0; f < 6; f++)
-                if (c[f] != 0.0) m = fmin(m, lab[nq[f]]);
-            if (m < lab[q]) {
-                lab[q] = m;
-                changed = 1.0;
-            }
-        }
-        if (block_sum(changed, sh) == 0.0) break;
-    }
-    // pm[q] = mean of y over the part of cell q (pm may not alias y)
-    auto part_means = [&](const double* y, bool from_bin, double* pm) {
-        double lo = (double)n;
-        for (int q = tid; q < n; q += nt) lo = fmin(lo, lab[q]);
-        double cur = block_min(lo, sh);
-        while (cur < (double)n) {
-            double sum = 0.0, cnt = 0.0, nxt = (double)n;
-            for (int q = tid; q < n; q += nt) {
-                if (lab[q] == cur) {
-                    sum += from_bin ? (double)bin[q] : y[q];
-                    cnt += 1.0;
-                } else if (lab[q] > cur) {
-                    nxt = fmin(nxt, lab[q]);
-                }
-            }
-            const double m = block_sum(sum, sh) / block_sum(cnt, sh);
-            for (int q = tid; q < n; q += nt)
-                if (lab[q] == cur) pm[q] = m;
-            cur = block_min(nxt, sh);
-        }
-        __syncthreads();
-    };
-    double part = 0.0;
-    double* bmean = s;  // free until the iteration
-    part_means(nullptr, true, bmean);
-    for (int q = tid; q < n; q += nt) x[q] = use_x0 ? (double)xout[q] : 0.0;
-
-    // A y for y in work (FP64), coefficients in T.
-    auto apply = [&](const double* y, double* out) {
-        __syncthreads();
-        for (int q = tid; q < n; q += nt) {
-            int i, j, k;
-            cell_ijk(d, q, i, j, k);
-            const Nbr nb = neighbours(d, q, i, j, k);
-            double csum, cv;
-            stencil_sums<double>(cx, cy, cz, y, q, nb, csum, cv);
-            out[q] = (csum * y[q] - cv) * inv_h2;
-        }
-        __syncthreads();
-    };
-
-    if (use_x0) apply(x, tv);
-    part = 0.0;
-    for (int q = tid; q < n; q += nt) {
-        const double rq = ((double)bin[q] - bmean[q]) - (use_x0 ? tv[q] : 0.0);
-        r[q] = rq;
-        rh[q] = rq;
-        p[q] = 0.0;
-        v[q] = 0.0;
-        part = fma(rq, rq, part);
-    }
-    const double bnorm2 = block_sum(part, sh);
-    const double tol2 = rtol * rtol * bnorm2;
-    double rho = 1.0, alpha = 1.0, omega = 1.0;
-    // squared residual of the current iterate and of the kept one (xb)
-    double rr_cur = bnorm2, rr_best = bnorm2;
-    for (int q = tid; q < n; q += nt) xb[q] = x[q];
-
-    int it = 0;  // iterations begun (each ends in a break or a full step)
-    if (bnorm2 > 0.0) {
-        for (; it < maxit; it++) {
-            part = 0.0;
-            for (int q = tid; q < n; q += nt) part = fma(rh[q], r[q], part);
-            const double rho1 = block_sum(part, sh);
-            if (rho1 == 0.0) break;
-            const double beta = (rho1 / rho) * (alpha / omega);
-            __syncthreads();
-            for (int q = tid; q < n; q += nt) p[q] = r[q] + beta * (p[q] - omega * v[q]);
-            apply(p, v);
-            part = 0.0;
-            for (int q = tid; q < n; q += nt) part = fma(rh[q], v[q], part);
-            const double rhv = block_sum(part, sh);
-            if (rhv == 0.0) break;
-            alpha = rho1 / rhv;
-            part = 0.0;
-            for (int q = tid; q < n; q += nt) {
-                s[q] = r[q] - alpha * v[q];
-                part = fma(s[q], s[q], part);
-            }
-            const double ss = block_sum(part, sh);
-            if (ss <= tol2) {
-                for (int q = tid; q < n; q += nt) x[q] += alpha * p[q];
-                rr_cur = ss;
-                break;
-            }
-            apply(s, tv);
-            double p1 = 0.0, p2 = 0.0;
-            for (int q = tid; q < n; q += nt) {
-                p1 = fma(tv[q], s[q], p1);
-                p2 = fma(tv[q], tv[q], p2);
-            }
-            const double ts = block_sum(p1, sh);
-            const double tt = block_sum(p2, sh);
-            if (tt == 0.0) {
-                for (int q = tid; q < n; q += nt) x[q] += alpha * p[q];
-                rr_cur = ss;
-                break;
-            }
-            omega = ts / tt;
-            part = 0.0;
-            for (int q = tid; q < n; q += nt) {
-                x[q] += alpha * p[q] + omega * s[q];
-                r[q] = s[q] - omega * tv[q];
-                part = fma(r[q], r[q], part);
-            }
-            const double rr = block_sum(part, sh);
-            rho = rho1;
-            rr_cur = rr;
-            if (rr <= tol2 || omega == 0.0) break;
-            if (rr < rr_best) {
-                rr_best = rr;
-                for (int q = tid; q < n; q += nt) xb[q] = x[q];
-            }
-        }
-    }
-    // x when converged, else the kept iterate (the threads that wrote xb read
-    // it back, so no barrier is needed before the copy)
-    if (!(rr_cur <= tol2))
-        for (int q = tid; q < n; q += nt) x[q] = xb[q];
-    if (iters && tid == 0) iters[0] += (double)(it < maxit ? it + (bnorm2 > 0.0 ? 1 : 0) : it);
-    __syncthreads();
-    part_means(x, false, tv);
-    for (int q = tid; q < n; q += nt) xout[q] = (T)(x[q] - tv[q]);
-}
-
-template <typename T>
-void launch_bottom(const Dims& d, const T* rhs, T* phi, const T* cx, const T* cy, const T* cz, double h2, double rtol,
-                   int maxit, int use_x0, double* work, double* iters, const double* skip_if_direct, hipStream_t s)
-{
-    long long n = d.n();
-    int nt = (int)((n + 63) / 64) * 64;
-    if (nt > 1024) nt = 1024;
-    hipLaunchKernelGGL((k_bottom<T>), dim3(1), dim3(nt), 0, s, d, rhs, phi, cx, cy, cz, h2, rtol, maxit, use_x0,
-                       work, iters, skip_if_direct);
-}
-
 // --------------------------------------------------------- FP64 level 0
 
 template <bool CELL>
@@ -672,9 +452,7 @@ void launch_ir_update(long long n, double* phi, const float* e, const double* s,
     template void launch_rb_pair<T>(const Dims&, const T*, T*, const T*, const Coef<T>&, T, int, const T*,           \
                                     hipStream_t);                                                                     \
     template void launch_resid_restrict<T>(const Dims&, const T*, const T*, const Coef<T>&, T, T*, hipStream_t);      \
-    template void launch_prolong<T>(const Dims&, T*, const T*, hipStream_t);                                          \
-    template void launch_bottom<T>(const Dims&, const T*, T*, const T*, const T*, const T*, double, double, int, int, \
-                                   double*, double*, const double*, hipStream_t);
+    template void launch_prolong<T>(const Dims&, T*, const T*, hipStream_t);
 MP_INST(float)
 MP_INST(double)
 

@@ -666,8 +666,8 @@ void vcycle(mp_ctx* c, int l, bool zero_init)
         return;
     }
     if (l == nlev - 1) {
-        // directly when G is usable, else BiCGStab (each kernel reads S_BINV
-        // and returns at once when the other one applies)
+        // directly when G is usable, else BiCGStab (each kernel reads
+        // S_BINV and returns at once when the other one applies)
         const double* ok = c->ginv ? c->dscal + S_BINV : nullptr;
         if (c->ginv) {
             wait_inverse(c);
@@ -1331,7 +1331,7 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
         d = Dims{d.nx / 2, d.ny / 2, d.nz / 2, d.px, d.py, d.pz};
         h *= 2.0;
     }
-    c->bottom_work = dalloc<double>(9 * c->lv.back().d.n(), e), good &= ok(c->bottom_work);
+    c->bottom_work = dalloc<double>(mp::kBottomWork * c->lv.back().d.n(), e), good &= ok(c->bottom_work);
     if (c->lv.back().d.n() <= mp::kDirectBottomCells)
         c->ginv = dalloc<double>(mp::kDirectBottomCells * mp::kDirectBottomCells, e), good &= ok(c->ginv);
     // single-workgroup coarse cycle: trailing levels of <= kCoarseCells cells,

@@ -138,21 +138,61 @@ __device__ __forceinline__ void cell_ijk(const Dims& d, long long q, int& i, int
     j = (int)(t - (long long)k * d.ny);
 }
 
-// Wavefront sum (every lane holds the total; lane 0's value is the one used).
+// v plus the value a DPP move of pattern C within rows of 16 lanes brings.
+template <int C>
+__device__ __forceinline__ double dpp_add(double v)
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)u, C, 0xf, 0xf, false);
+    const unsigned hi = (unsigned)__builtin_amdgcn_mov_dpp((int)(unsigned)(u >> 32), C, 0xf, 0xf, false);
+    return v + __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
+}
+
+// v of one half (or of one row of each pair) plus v of the other, in every
+// lane: the builtin returns both sides of the exchange.
+template <bool ROWS>
+__device__ __forceinline__ double swap_add(double v)
+{
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned l = (unsigned)u, h = (unsigned)(u >> 32);
+    const auto lo = ROWS ? __builtin_amdgcn_permlane16_swap(l, l, false, false)
+                         : __builtin_amdgcn_permlane32_swap(l, l, false, false);
+    const auto hi = ROWS ? __builtin_amdgcn_permlane16_swap(h, h, false, false)
+                         : __builtin_amdgcn_permlane32_swap(h, h, false, false);
+    return __builtin_bit_cast(double, ((unsigned long long)hi[0] << 32) | lo[0]) +
+           __builtin_bit_cast(double, ((unsigned long long)hi[1] << 32) | lo[1]);
+}
+
+// Wavefront sum: the butterfly over lane distances 32, 16, 8, 4, 2, 1, so every
+// lane holds the same bits.  Half and row exchanges (permlane swaps) and DPP
+// moves in the vector pipeline instead of LDS permutes: the sums stand in
+// serial chains (Krylov iterations, block reductions), where an LDS permute's
+// latency counts twice per step.  A rotation by 8 or 4 within 16 lanes brings the value
+// of the partner lane because the lanes are already equal modulo the larger
+// distances.
 __device__ __forceinline__ double wave_sum(double v)
 {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
+    v = swap_add<false>(v);  // distance 32
+    v = swap_add<true>(v);   // 16
+    v = dpp_add<0x128>(v);   // 8: row_ror:8
+    v = dpp_add<0x124>(v);   // 4: row_ror:4
+    v = dpp_add<0x4e>(v);    // 2: quad_perm [2,3,0,1]
+    v = dpp_add<0xb1>(v);    // 1: quad_perm [1,0,3,2]
     return v;
 }
 
-// Wavefront sum whose value is lane 0's result broadcast to every lane, so all
-// lanes take identical branches on it.
-__device__ __forceinline__ double wave_sum_bcast(double v)
+// The value of lane 0 in every lane, held uniformly (so that all lanes take
+// identical branches on it).
+__device__ __forceinline__ double lane0(double v)
 {
-    v = wave_sum(v);
-    return __shfl(v, 0, kWave);
+    const unsigned long long u = __builtin_bit_cast(unsigned long long, v);
+    const unsigned lo = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)u);
+    const unsigned hi = (unsigned)__builtin_amdgcn_readfirstlane((int)(unsigned)(u >> 32));
+    return __builtin_bit_cast(double, ((unsigned long long)hi << 32) | lo);
 }
+
+// Wavefront sum, uniform.
+__device__ __forceinline__ double wave_sum_bcast(double v) { return lane0(wave_sum(v)); }
 
 // Block sum in a fixed order; every thread receives the same value.  Works
 // for 1D, 2D and 3D blocks whose thread count is a multiple of 64 (full

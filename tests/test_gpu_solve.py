@@ -182,6 +182,59 @@ def test_direct_bottom_matches_sparse_lu(precision, shape, bc):
     ctx.close()
 
 
+# the bottom kernel's forms end at 256, 512, 1024, 2048, 3072 and 5120 cells
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("shape,bc", [((5, 7, 7), (1, 1, 1)), ((256, 1, 1), (1, 0, 0)), ((257, 1, 1), (0, 0, 0)),
+                                      ((7, 9, 9), (0, 0, 1)), ((9, 9, 13), (1, 0, 1)), ((13, 13, 13), (0, 0, 0)),
+                                      ((15, 13, 17), (1, 1, 1)), ((17, 17, 19), (0, 1, 1))])
+def test_krylov_bottom_matches_sparse_lu(precision, shape, bc):
+    """One-level grids of odd extents are solved by the bottom kernel alone."""
+    nx, ny, nz = shape
+    say("krylov bottom", shape, bc, precision)
+    h = 1.0 / max(shape)
+    cx, cy, cz = W.random_coefs(nx, ny, nz, bc, 331)
+    rhs = W.random_cells(nx, ny, nz, 332)
+    ctx = mproj.Context(nx, ny, nz, h=h, bc=bc, precision=precision, rtol=1e-12)
+    ctx.set_coefs(T(cx), T(cy), T(cz))
+    x, info = ctx.solve(T(rhs))
+    ref = pins.bordered_solve(pins.operator(nx, ny, nz, h, bc, cx, cy, cz), rhs).reshape(nz, ny, nx)
+    # error <= condition number (about 4 max(n)^2) times the residual
+    assert rel(N(x), ref) < 4e-12 * max(shape) ** 2
+    assert info["levels"] == 1 and info["bottom_iters_total"] > 0
+    ctx.close()
+
+
+@pytest.mark.parametrize("n", [7, 11, 15, 19])
+def test_krylov_bottom_on_a_split_grid(n):
+    """A one-level grid cut in two by zero faces and holding an isolated cell:
+    every part mean-zero, an iteration cap that ends early still returns a
+    finite best iterate."""
+    bc = (1, 1, 1)
+    cx, cy, cz = W.random_coefs(n, n, n, bc, 341)
+    cx[:, :, n // 2] = 0.0
+    i, j, k = 1, 2, 3
+    cx[k, j, i] = cx[k, j, i + 1] = cy[k, j, i] = cy[k, j + 1, i] = cz[k, j, i] = cz[k + 1, j, i] = 0.0
+    rhs = W.random_cells(n, n, n, 342)
+    rhs[k, j, i] = 0.0
+    for half in (slice(0, n // 2), slice(n // 2, n)):
+        m = np.zeros((n, n, n), dtype=bool)
+        m[:, :, half] = True
+        m[k, j, i] = False
+        rhs[m] -= rhs[m].mean()
+    g = oracle.Grid(n, n, n, 1.0 / n, bc)
+    ctx = mproj.Context(n, n, n, h=1.0 / n, bc=bc, precision="fp64", rtol=1e-10)
+    ctx.set_coefs(T(cx), T(cy), T(cz))
+    x, _ = ctx.solve(T(rhs))
+    assert oracle.residual_norm(g, cx, cy, cz, rhs, N(x)) <= 1e-9
+    ctx.close()
+    ctx = mproj.Context(n, n, n, h=1.0 / n, bc=bc, precision="fp64", rtol=1e-10, bottom_max_iter=2, max_outer=1)
+    ctx.set_coefs(T(cx), T(cy), T(cz))
+    x, _ = ctx.solve(T(rhs), allow_not_converged=True)
+    assert np.isfinite(N(x)).all()
+    assert oracle.residual_norm(g, cx, cy, cz, rhs, N(x)) <= 1.0
+    ctx.close()
+
+
 @pytest.mark.parametrize("precision,coarse_cycle", [("fp64", True), ("fp64", False), ("mixed", True), ("mixed", False)])
 @pytest.mark.parametrize("n", [16, 32])
 def test_disconnected_bottom_falls_back_to_conjugate_gradients(precision, coarse_cycle, n):
