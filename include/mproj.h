@@ -96,8 +96,9 @@ typedef struct mp_config {
                                 HIP events (mp_info.smooth_*) */
     int smoother;            /* MP_SMOOTH_AUTO: both colours of a sweep in one
                                 launch wherever it pays: register-blocked
-                                levels in MIXED whose rows are 128, 256, 384
-                                or 512 cells, face-coefficient levels of >= 4M cells
+                                levels in MIXED whose rows of up to 512 cells
+                                split into equal strips of 2, 4, 6 or 8 cells
+                                over a wavefront, face-coefficient levels of >= 4M cells
                                 (tiled), and the other FP32 levels below the
                                 finest of <= 64^3 cells with even extents (one
                                 red and one black cell per thread); one launch
@@ -113,7 +114,8 @@ typedef struct mp_config {
                                 kernels (a strip of 2-8 x cells in 2-4 rows
                                 per lane, marching along z) when its
                                 coefficients are cell values (after
-                                mp_map_base_state), nx % 128 == 0,
+                                mp_map_base_state), nx % 128 == 0 (or nx
+                                even, >= 64 and more than 2^18 cells),
                                 ny % 4 == 0, nz is even and >= 4, and the
                                 solution array is 16-byte aligned; 0: one
                                 cell per thread.  Same bits in FP64. */

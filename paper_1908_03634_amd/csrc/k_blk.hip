@@ -19,7 +19,7 @@
 //
 // Shape: 256-thread blocks of 4 wavefronts; block (bx, by, bz) covers columns
 // [128 M bx, 128 M (bx + 1)), rows [4R by, 4R (by + 1)) (R per wavefront) and
-// planes [lz bz, lz (bz + 1)).  Requires nx % 128 == 0, ny % 4 == 0 and an
+// planes [lz bz, lz (bz + 1)).  Requires an even nx >= 64, ny % 4 == 0 and an
 // even nz >= 4; arrays 16-byte aligned.
 #include "mp_blk.h"
 #include "mp_device.h"
@@ -29,7 +29,11 @@
 
 namespace mp {
 
-bool blk_supported(const Dims& d) { return d.nx % 128 == 0 && d.ny % 4 == 0 && d.nz >= 4 && d.nz % 2 == 0; }
+// Rows of at least 64 cells: at least half of a wavefront's lanes hold cells.
+bool blk_supported(const Dims& d)
+{
+    return d.nx >= 64 && d.nx % 2 == 0 && d.ny % 4 == 0 && d.nz >= 4 && d.nz % 2 == 0;
+}
 
 // ------------------------------------------------------------------ smoother
 
@@ -186,8 +190,9 @@ __global__ __launch_bounds__(BK_T) void k_gs_blk(Dims d, int lz, T* __restrict__
 #pragma unroll
                 for (int q = 1; q < 2 * M; q += 2) upd(q);
             }
-            st_strip<T, M>(x, bk + roff[t + 1] + g.xi, out);
+            if (g.on) st_strip<T, M>(x, bk + roff[t + 1] + g.xi, out);
             if constexpr (IRU) {
+                if (!g.on) continue;
                 const double sc = irs[0];
                 double* pp = phi + bk + roff[t + 1] + g.xi;
 #pragma unroll
@@ -351,7 +356,7 @@ __global__ __launch_bounds__(BK_T) void k_rr_blk(Dims d, int lz, const T* __rest
                     for (int bb = 0; bb < 2; bb++)
 #pragma unroll
                         for (int a = 0; a < 2; a++) acc += r[cz][2 * u + bb].v[2 * m + a];
-                o[m] = T(0.125) * acc;
+                if (g.on) o[m] = T(0.125) * acc;
             }
         }
     }
@@ -401,10 +406,10 @@ __global__ __launch_bounds__(BK_T) void k_resid64_blk(Dims d, int lz, const doub
                 Strip<float, M> f;
 #pragma unroll
                 for (int c = 0; c < 2 * M; c++) {
-                    acc = fma(r[t].v[c], r[t].v[c], acc);
+                    if (g.on) acc = fma(r[t].v[c], r[t].v[c], acc);
                     f.v[c] = (float)(r[t].v[c] * is);
                 }
-                if (r32) st_strip<float, M>(r32, bk + roff[t + 1] + g.xi, f);
+                if (r32 && g.on) st_strip<float, M>(r32, bk + roff[t + 1] + g.xi, f);
             }
             ring_shift<double, M, R>(xm, x0, cm, c0, q);
             q = nxt;

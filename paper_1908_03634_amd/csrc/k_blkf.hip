@@ -189,7 +189,7 @@ __global__ __launch_bounds__(BK_T) void k_gs_blkf(Dims d, int lz, T* __restrict_
 #pragma unroll
                 for (int q = 1; q < 2 * M; q += 2) upd(q);
             }
-            st_strip<T, M>(x, bk + roff[t + 1] + g.xi, out);
+            if (g.on) st_strip<T, M>(x, bk + roff[t + 1] + g.xi, out);
         }
 #pragma unroll
         for (int t = 0; t < R; t++) {
@@ -308,7 +308,7 @@ __global__ __launch_bounds__(BK_T) void k_rr_blkf(Dims d, int lz, const T* __res
                     for (int bb = 0; bb < 2; bb++)
 #pragma unroll
                         for (int a = 0; a < 2; a++) acc += r[cz][2 * u + bb].v[2 * m + a];
-                o[m] = T(0.125) * acc;
+                if (g.on) o[m] = T(0.125) * acc;
             }
         }
     }
@@ -339,11 +339,11 @@ static void gsf_mode(int mode, const Dims& d, T* x, const T* b, const Coef<T>& c
     }
 }
 
-// Strip width: pairs in FP64 and when nx / 128 is odd, else strips of 4.
+// Strip width: strips of 4 in FP32 rows of whole 256-cell wavefronts, else pairs.
 template <typename T>
 static bool face_pairs(const Dims& d)
 {
-    return sizeof(T) == 8 || (d.nx / 128) % 2 != 0;
+    return sizeof(T) == 8 || d.nx % 256 != 0;
 }
 
 template <typename T>

@@ -7,7 +7,9 @@
 // twice (32 bytes per cell in FP32); here one pass does both (16 bytes).
 //
 // Wavefront w of a workgroup holds row j0 - 2 + w of every plane (a whole
-// row: nx = 128 M, 2M cells per lane), so the R + 4 wavefronts span the R
+// row of at most 128 M cells, 2M per lane: rows of 160 cells keep 40 lanes of
+// 64 busy and still sweep 160 x 160 x 320 in 38 us, against 111 us by two
+// one-cell colour passes; 192^3 34 us against 80 us), so the R + 4 wavefronts span the R
 // owned rows, one row on each side whose red is recomputed and one more on
 // each side that only supplies old values.  The workgroup marches along z
 // through a chunk of planes; each wavefront keeps its own cells of planes
@@ -38,18 +40,19 @@
 
 namespace mp {
 
-bool fsw_supported(const Dims& d)
+// Strip width M (2M cells per lane) of the sweep on rows of nx cells, 0 where
+// it does not run: a whole row per wavefront.  Lanes past the row's end stand
+// for its wrap partners: the lane after the last strip loads the first strip
+// and lane 63 the last one, so that the wavefront rotations also close a
+// periodic row that does not fill the wavefront (with one lane past the end,
+// those two would be the same lane: not supported).
+static int fsw_pairs(const Dims& d)
 {
-    return blk_supported(d) && (d.nx == 128 || d.nx == 256 || d.nx == 384 || d.nx == 512);
+    const int m = row_pairs(d);
+    return m && d.px && d.nx / (2 * m) == kWave - 1 ? 0 : m;
 }
 
-// Rows of 192 cells between walls in x (the 384^3 box's second level): the
-// strips of 256-cell rows, lanes 48-63 past the row's end idle (they load the
-// row's first cells, and store nothing).
-bool fsw_narrow_supported(const Dims& d)
-{
-    return d.nx == 192 && !d.px && d.ny % 4 == 0 && d.nz >= 4 && d.nz % 2 == 0;
-}
+bool fsw_supported(const Dims& d) { return blk_supported(d) && fsw_pairs(d) != 0; }
 
 // The M cells of one parity (q even or q odd) of a lane's strip.
 template <typename T, int M>
@@ -243,7 +246,7 @@ struct FsLds {
     const double* __restrict__ irs;
     bool phi_fresh;  // phi is zero on entry: written, not read
     bool lane_live;  // the lane's strip lies in the row (rows narrower than 2 M x 64 cells)
-    int xe;          // the strip's first column, 0 for a lane past the row's end
+    int xe;          // the column the lane's strip is loaded from
     T h2;
     T (*sx)[NW * NX];
     T (*sc)[NW * NX];
@@ -366,6 +369,7 @@ __global__ __launch_bounds__(kWave*(R + 4)) void k_fsw_lds(Dims d, int lz, const
     g.j0 = (int)by * R;
     g.z0 = (int)bz * lz;
     g.z1 = min(g.z0 + lz, d.nz);
+    g.on = true;
     g.hal = false;
     g.hcol = 0;
     g.wl = !PXY && g.xi == 0 && !d.px;
@@ -375,12 +379,13 @@ __global__ __launch_bounds__(kWave*(R + 4)) void k_fsw_lds(Dims d, int lz, const
     const int t = threadIdx.x / kWave;  // row of the workgroup
     F f{d, g};
     f.j = g.j0 - 2 + t;
-    f.jw = wrap_row(d, f.j);
+    // (rows beyond the last red row's neighbour only fill the workgroup)
+    f.jw = wrap_row(d, min(f.j, d.ny + 1));
     f.red_row = t >= 1 && t <= R + 2;
     f.black_row = t >= 2 && t <= R + 1 && f.j < d.ny;
     f.sz = (long long)d.nx * d.ny;
     f.lane_live = g.xi < d.nx;
-    f.xe = f.lane_live ? g.xi : 0;
+    f.xe = f.lane_live ? g.xi : g.lane == kWave - 1 ? d.nx - 2 * M : 0;
     f.roff = (long long)f.jw * d.nx + f.xe;
     f.nxc = d.nx >> 1;
     f.szc = (long long)f.nxc * (d.ny >> 1);
@@ -466,7 +471,7 @@ __global__ __launch_bounds__(kWave*(R + 4)) void k_fsw_lds(Dims d, int lz, const
     }
 }
 
-// Launch shape by strip width M (2M cells per lane, rows of 128 M cells):
+// Launch shape by strip width M (2M cells per lane, rows of up to 128 M cells):
 // rows owned by a workgroup (R + 4 wavefronts) and planes loaded ahead (D).
 // Rows of up to 256 cells: 8 rows, 12 wavefronts, three per SIMD.  Rows of
 // 384 and 512 cells hold 6 or 8 cells per lane in every plane slot: 4 rows,
@@ -580,10 +585,10 @@ template <typename T>
 void launch_fsw_blk(const Dims& d, const T* xo, T* xn, const T* b, const T* cc, T h2, int mode, const T* ec,
                     double* phi, const double* irs, int irf, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s)
 {
-    switch (d.nx) {
-    case 512: fsw_mode<T, 4>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s); break;
-    case 384: fsw_mode<T, 3>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s); break;
-    case 256: fsw_mode<T, 2>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s); break;
+    switch (fsw_pairs(d)) {
+    case 4: fsw_mode<T, 4>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s); break;
+    case 3: fsw_mode<T, 3>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s); break;
+    case 2: fsw_mode<T, 2>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s); break;
     default: fsw_mode<T, 1>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s); break;
     }
 }
@@ -612,11 +617,10 @@ template <typename T>
 void launch_fsw_blkf(const Dims& d, const T* xo, T* xn, const T* b, const Coef<T>& c, T h2, int mode, const T* ec,
                      hipStream_t s)
 {
-    switch (d.nx) {
-    case 512: fswf_mode<T, 4>(mode, d, xo, xn, b, c, h2, ec, s); break;
-    case 384: fswf_mode<T, 3>(mode, d, xo, xn, b, c, h2, ec, s); break;
-    case 256:
-    case 192: fswf_mode<T, 2>(mode, d, xo, xn, b, c, h2, ec, s); break;
+    switch (fsw_pairs(d)) {
+    case 4: fswf_mode<T, 4>(mode, d, xo, xn, b, c, h2, ec, s); break;
+    case 3: fswf_mode<T, 3>(mode, d, xo, xn, b, c, h2, ec, s); break;
+    case 2: fswf_mode<T, 2>(mode, d, xo, xn, b, c, h2, ec, s); break;
     default: fswf_mode<T, 1>(mode, d, xo, xn, b, c, h2, ec, s); break;
     }
 }

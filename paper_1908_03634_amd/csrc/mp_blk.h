@@ -102,7 +102,8 @@ __device__ __forceinline__ Strip<T, M> zero_strip()
 }
 
 struct BlkGeo {
-    int lane, xi, j0, z0, z1;
+    int lane, xi, j0, z0, z1;  // xi: the strip's first column (0 for a lane past the row's end)
+    bool on;      // the lane's strip lies in the row
     bool hal;     // lane 0 or 63 of a wavefront that does not span the row: loads a halo column
     int hcol;     // that column (the wrap partner when periodic)
     bool wl, wr;  // the strip's first / last cell touches a Neumann wall
@@ -125,6 +126,9 @@ __device__ __forceinline__ void blk_tile(unsigned& bx, unsigned& by, unsigned& b
     bz = p / (gx * gy);
 }
 
+// A row's last wavefront may have lanes past the row's end: they load the row's
+// first strip (so that the last strip's next lane holds its neighbour across a
+// periodic wrap) and store nothing.
 template <int M, int R>
 __device__ __forceinline__ BlkGeo blk_geo(const Dims& d, int lz)
 {
@@ -135,7 +139,9 @@ __device__ __forceinline__ BlkGeo blk_geo(const Dims& d, int lz)
     g.lane = threadIdx.x & (kWave - 1);
     const int w = threadIdx.x / kWave;
     const int x0 = (int)bx * W;
-    g.xi = x0 + 2 * M * g.lane;
+    const int xs = x0 + 2 * M * g.lane;
+    g.on = xs < d.nx;
+    g.xi = g.on ? xs : 0;
     g.j0 = ((int)by * BK_W + w) * R;
     g.live = g.j0 < d.ny;
     g.z0 = (int)bz * lz;
@@ -143,8 +149,8 @@ __device__ __forceinline__ BlkGeo blk_geo(const Dims& d, int lz)
     const bool whole = W == d.nx;
     g.hal = !whole && (g.lane == 0 || g.lane == kWave - 1);
     g.hcol = g.lane == 0 ? (x0 > 0 ? x0 - 1 : d.nx - 1) : (x0 + W < d.nx ? x0 + W : 0);
-    g.wl = g.xi == 0 && !d.px;
-    g.wr = g.xi + 2 * M == d.nx && !d.px;
+    g.wl = xs == 0 && !d.px;
+    g.wr = xs + 2 * M == d.nx && !d.px;
     g.yfirst = g.j0 > 0 || d.py;
     g.ylast = g.j0 + R < d.ny || d.py;
     return g;
@@ -254,14 +260,25 @@ __device__ __forceinline__ Strip<T, M> add_e(const Strip<T, M>& x, const EStrip<
 
 // ------------------------------------------------------------ launch shape
 
-// Strip width M (pairs per lane): the whole row in one wavefront when
-// nx / 128 <= 4, else the largest of 4, 3, 2, 1 that divides nx / 128.
+// Strip width M (pairs per lane) that takes a whole row into one wavefront:
+// the smallest of 1 to 4 that reaches across the row and divides it, 0 if none.
+inline int row_pairs(const Dims& d)
+{
+    for (int m = 1; m <= 4; m++)
+        if (d.nx <= 128 * m && d.nx % (2 * m) == 0) return m;
+    return 0;
+}
+
+// Strip width of the blocked kernels: the whole row in one wavefront where
+// row_pairs allows, else the largest of 4, 3, 2, 1 that tiles the row in whole
+// wavefronts, else pairs with a partly filled last wavefront.
 inline int strip_pairs(const Dims& d)
 {
-    const int t = d.nx / 128;
-    if (t <= 4) return t;
-    for (int m = 4; m > 1; m--)
-        if (t % m == 0) return m;
+    const int r = row_pairs(d);
+    if (r) return r;
+    if (d.nx % 128 == 0)
+        for (int m = 4; m > 1; m--)
+            if (d.nx / 128 % m == 0) return m;
     return 1;
 }
 
@@ -276,7 +293,7 @@ constexpr int rows_for(int M)
 // `min_blocks` blocks, then doubled while it has more than `max_blocks`.
 inline dim3 blk_grid(const Dims& d, int M, int rows, long long min_blocks, long long max_blocks, int& lz)
 {
-    const long long gx = d.nx / (128 * M), gy = (d.ny + rows * BK_W - 1) / (rows * BK_W);
+    const long long gx = (d.nx + 128 * M - 1) / (128 * M), gy = (d.ny + rows * BK_W - 1) / (rows * BK_W);
     auto nb = [&](int l) { return gx * gy * ((d.nz + l - 1) / l); };
     lz = 16;
     while (lz > 2 && nb(lz) < min_blocks) lz >>= 1;

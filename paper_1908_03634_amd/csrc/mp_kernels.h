@@ -228,8 +228,9 @@ template <typename T>
 void launch_gs_blk(const Dims& d, T* x, const T* b, const T* cc, T h2, int colour, int mode, const T* ec,
                    double* phi, const double* irs, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s);
 // Both colours of one red-black sweep in one pass, out of place (xo -> xn),
-// in FP32 when fsw_supported(d) (blocked layout, nx = 128, 256, 384 or 512;
-// whole rows per workgroup, rows exchanged through LDS).  Modes:
+// in FP32 when fsw_supported(d) (blocked layout, rows of at most 512 cells that
+// split into equal strips over a wavefront; whole rows per workgroup, rows
+// exchanged through LDS).  Modes:
 //   FS_PLAIN:   xo as stored;
 //   FS_ZERO:    xo is zero (not read);
 //   FS_PROLONG: xo + e of each cell's parent coarse cell (ec), i.e. the
@@ -248,9 +249,6 @@ template <typename T>
 void launch_rb_pair(const Dims& d, const T* xo, T* xn, const T* b, const Coef<T>& c, T h2, int mode, const T* ec,
                     hipStream_t s);
 bool fsw_supported(const Dims& d);
-// Rows of 192 cells with walls in x: the stored-face sweep below on 256-cell
-// strips, the lanes past the row's end idle.
-bool fsw_narrow_supported(const Dims& d);
 template <typename T>
 void launch_fsw_blk(const Dims& d, const T* xo, T* xn, const T* b, const T* cc, T h2, int mode, const T* ec,
                     double* phi, const double* irs, int irf, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s);

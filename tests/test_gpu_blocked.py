@@ -209,3 +209,48 @@ def test_blocked_projection_kernels(shape, bc, precision, split):
         assert np.abs(a[q] - b[q]).max() <= 1e-10 * np.abs(b[q]).max()
     assert a[4]["rhs_norm"] == pytest.approx(b[4]["rhs_norm"], rel=1e-13)
     assert a[4]["div_defect"] <= 2e-12 and b[4]["div_defect"] <= 2e-12
+
+
+# rows that leave lanes of their last wavefront without cells: half filled (64),
+# one lane short of a wavefront (126, 252, 504, whose one-pass sweep needs walls
+# in x), strips of 2 to 8 cells, and pairs tiled with a partly filled last
+# wavefront (130, 250, 516)
+PARTIAL = [(64, 8, 4), (100, 12, 6), (126, 8, 6), (130, 8, 4), (160, 20, 10), (192, 36, 32), (250, 4, 4),
+           (252, 12, 6), (288, 8, 6), (320, 12, 10), (504, 8, 4), (516, 4, 4)]
+
+
+@pytest.mark.parametrize("bc", BCS)
+@pytest.mark.parametrize("shape", PARTIAL)
+def test_partly_filled_rows_equal_the_one_cell_kernels(shape, bc):
+    """FP64 solves bitwise; FP32 bitwise through a refinement step (smoother
+    "fused": the blocked kernels also on grids too small for them to pay)."""
+    say("partial rows", shape, bc)
+    p = _problem(shape, bc, 5400 + sum(shape))
+    rhs = W.random_cells(*shape, 5500 + sum(shape))
+    xa, ia = _solve(p, "fp64", True, rhs, rtol=1e-11, smoother="fused")
+    xb, ib = _solve(p, "fp64", False, rhs, rtol=1e-11)
+    assert np.array_equal(xa, xb) and ia["vcycles"] == ib["vcycles"]
+    xa, _ = _solve(p, "mixed", True, rhs, max_outer=1, smoother="fused")
+    xb, _ = _solve(p, "mixed", False, rhs, max_outer=1)
+    assert np.array_equal(xa, xb)
+
+
+@pytest.mark.parametrize("bc", BCS)
+@pytest.mark.parametrize("shape", [(160, 64, 64), (192, 48, 32), (200, 40, 64), (100, 52, 64)])
+def test_partly_filled_rows_with_face_coefficients(shape, bc):
+    """The same kernels on stored faces: a finest level of more than 64^3 cells
+    set by the caller, by one-pass sweeps and by colour passes, bitwise through a
+    refinement step."""
+    say("partial rows, faces", shape, bc)
+    nx, ny, nz = shape
+    cs = [T(c) for c in W.random_coefs(nx, ny, nz, bc, 5600)]
+    rhs = T(W.random_cells(nx, ny, nz, 5700))
+    out = {}
+    for key, kw in (("one cell", dict(blocked=False)), ("sweep", {}), ("colours", dict(smoother="per_colour"))):
+        ctx = mproj.Context(nx, ny, nz, bc=bc, precision="mixed", max_outer=1, **kw)
+        ctx.set_coefs(*cs)
+        x, _ = ctx.solve(rhs, allow_not_converged=True)
+        out[key] = N(x)
+        ctx.close()
+    assert np.array_equal(out["sweep"], out["one cell"])
+    assert np.array_equal(out["colours"], out["one cell"])
