@@ -96,9 +96,9 @@ typedef struct mp_config {
                                 HIP events (mp_info.smooth_*) */
     int smoother;            /* MP_SMOOTH_AUTO: both colours of a sweep in one
                                 launch wherever it pays: register-blocked
-                                levels in MIXED whose rows of up to 512 cells
-                                split into equal strips of 2, 4, 6 or 8 cells
-                                over a wavefront, face-coefficient levels of >= 4M cells
+                                levels whose rows of up to 512 cells (FP64:
+                                256) split into equal strips of 2, 4, 6 or 8
+                                cells over a wavefront, face-coefficient levels of >= 4M cells
                                 (tiled), and the other FP32 levels below the
                                 finest of <= 64^3 cells with even extents (one
                                 red and one black cell per thread); one launch

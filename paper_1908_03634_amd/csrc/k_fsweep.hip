@@ -53,6 +53,9 @@ static int fsw_pairs(const Dims& d)
 }
 
 bool fsw_supported(const Dims& d) { return blk_supported(d) && fsw_pairs(d) != 0; }
+// FP64: rows of at most 256 cells (the plane slots of longer rows' strips exceed
+// the registers of two wavefronts per SIMD).
+bool fsw64_supported(const Dims& d) { return fsw_supported(d) && fsw_pairs(d) <= 2; }
 
 // The M cells of one parity (q even or q odd) of a lane's strip.
 template <typename T, int M>
@@ -473,13 +476,18 @@ __global__ __launch_bounds__(kWave*(R + 4)) void k_fsw_lds(Dims d, int lz, const
 
 // Launch shape by strip width M (2M cells per lane, rows of up to 128 M cells):
 // rows owned by a workgroup (R + 4 wavefronts) and planes loaded ahead (D).
-// Rows of up to 256 cells: 8 rows, 12 wavefronts, three per SIMD.  Rows of
+// FP32 rows of up to 256 cells: 8 rows, 12 wavefronts, three per SIMD.  Rows of
 // 384 and 512 cells hold 6 or 8 cells per lane in every plane slot: 4 rows,
 // 8 wavefronts, two per SIMD, which the larger strips need for registers.
-template <int M, int MODE, bool IRU, bool CELL>
+// FP64 strips take twice the registers: 8 rows of up to 128 cells, 4 of up to
+// 256, without a plane ahead (128^3 stored faces: 19.3 us; 4 rows 19.9, a plane
+// ahead 23.2).  An FP64 sweep of 256^3 cell coefficients takes 145 us, 3.7 TB/s,
+// against 206 us for two colour passes: five correctly rounded divisions per
+// cell keep the vector pipeline busier than HBM.
+template <typename T, int M, int MODE, bool IRU, bool CELL>
 struct FswShape {
-    static constexpr int R = M <= 2 ? 8 : 4;
-    static constexpr int D = M <= 3 ? 1 : 0;
+    static constexpr int R = sizeof(T) == 8 ? (M == 1 ? 8 : 4) : M <= 2 ? 8 : 4;
+    static constexpr int D = sizeof(T) == 8 ? 0 : M <= 3 ? 1 : 0;
 };
 constexpr int kFswMinPlanes = 8;
 
@@ -496,7 +504,7 @@ constexpr int kFswMinPlanes = 8;
 template <typename T, int MODE, int M, bool IRU, bool CELL, bool PXY>
 static int fsw_chunk(const Dims& d, long long gy)
 {
-    constexpr int R = FswShape<M, MODE, IRU, CELL>::R, D = FswShape<M, MODE, IRU, CELL>::D, NS = D + 4;
+    constexpr int R = FswShape<T, M, MODE, IRU, CELL>::R, D = FswShape<T, M, MODE, IRU, CELL>::D, NS = D + 4;
     static int resident = 0;  // workgroups resident on the device at once
     if (resident == 0) {
         int dev = 0, ncu = 0, per_cu = 0;
@@ -528,7 +536,7 @@ static void fsw_launch_p(const Dims& d, const T* xo, T* xn, const T* b, const T*
                          T h2, const T* ec, double* phi, const double* irs, int irf, hipEvent_t ev0, hipEvent_t ev1,
                          hipStream_t s)
 {
-    constexpr int R = FswShape<M, MODE, IRU, CELL>::R, D = FswShape<M, MODE, IRU, CELL>::D;
+    constexpr int R = FswShape<T, M, MODE, IRU, CELL>::R, D = FswShape<T, M, MODE, IRU, CELL>::D;
     const long long gy = (d.ny + R - 1) / R;
     const int lz = fsw_chunk<T, MODE, M, IRU, CELL, PXY>(d, gy);
     const dim3 grid(1, (unsigned)gy, (unsigned)((d.nz + lz - 1) / lz));
@@ -556,7 +564,9 @@ template <typename T, int M>
 static void fsw_mode(int mode, const Dims& d, const T* xo, T* xn, const T* b, const T* cc, T h2, const T* ec,
                      double* phi, const double* irs, int irf, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s)
 {
-    if (phi) {
+    if constexpr (sizeof(T) == 8) {
+        (void)phi;
+    } else if (phi) {
         // the refinement update rides on the last sweep of a V-cycle
         if (mode == FS_PROLONG)
             fsw_launch<T, FS_PROLONG, M, true, true>(d, xo, xn, b, cc, nullptr, nullptr, h2, ec, phi, irs, irf, ev0, ev1,
@@ -586,8 +596,12 @@ void launch_fsw_blk(const Dims& d, const T* xo, T* xn, const T* b, const T* cc, 
                     double* phi, const double* irs, int irf, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s)
 {
     switch (fsw_pairs(d)) {
-    case 4: fsw_mode<T, 4>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s); break;
-    case 3: fsw_mode<T, 3>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s); break;
+    case 4:
+        if constexpr (sizeof(T) == 4) fsw_mode<T, 4>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s);
+        break;
+    case 3:
+        if constexpr (sizeof(T) == 4) fsw_mode<T, 3>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s);
+        break;
     case 2: fsw_mode<T, 2>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s); break;
     default: fsw_mode<T, 1>(mode, d, xo, xn, b, cc, h2, ec, phi, irs, irf, ev0, ev1, s); break;
     }
@@ -618,16 +632,23 @@ void launch_fsw_blkf(const Dims& d, const T* xo, T* xn, const T* b, const Coef<T
                      hipStream_t s)
 {
     switch (fsw_pairs(d)) {
-    case 4: fswf_mode<T, 4>(mode, d, xo, xn, b, c, h2, ec, s); break;
-    case 3: fswf_mode<T, 3>(mode, d, xo, xn, b, c, h2, ec, s); break;
+    case 4:
+        if constexpr (sizeof(T) == 4) fswf_mode<T, 4>(mode, d, xo, xn, b, c, h2, ec, s);
+        break;
+    case 3:
+        if constexpr (sizeof(T) == 4) fswf_mode<T, 3>(mode, d, xo, xn, b, c, h2, ec, s);
+        break;
     case 2: fswf_mode<T, 2>(mode, d, xo, xn, b, c, h2, ec, s); break;
     default: fswf_mode<T, 1>(mode, d, xo, xn, b, c, h2, ec, s); break;
     }
 }
 
-template void launch_fsw_blk<float>(const Dims&, const float*, float*, const float*, const float*, float, int,
-                                    const float*, double*, const double*, int, hipEvent_t, hipEvent_t, hipStream_t);
-template void launch_fsw_blkf<float>(const Dims&, const float*, float*, const float*, const Coef<float>&, float, int,
-                                     const float*, hipStream_t);
+#define FSW_INST(T)                                                                                               \
+    template void launch_fsw_blk<T>(const Dims&, const T*, T*, const T*, const T*, T, int, const T*, double*,     \
+                                    const double*, int, hipEvent_t, hipEvent_t, hipStream_t);                     \
+    template void launch_fsw_blkf<T>(const Dims&, const T*, T*, const T*, const Coef<T>&, T, int, const T*,       \
+                                     hipStream_t);
+FSW_INST(float)
+FSW_INST(double)
 
 }  // namespace mp

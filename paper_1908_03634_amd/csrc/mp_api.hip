@@ -507,9 +507,8 @@ void smooth(mp_ctx* c, int l, bool zero_init, const T* ec, bool last = false)
         // written, b and the three faces read; 1/8 word of coarse correction
         const double words = (zero_init ? 5.0 : 6.0) + (ec ? 0.125 : 0.0);
         timed_begin(c, tm);
-        if constexpr (sizeof(T) == 4)
-            mp::launch_fsw_blkf<T>(L.d, (const T*)L.x, (T*)L.x2, (const T*)L.b, C, h2,
-                                   zero_init ? mp::FS_ZERO : ec ? mp::FS_PROLONG : mp::FS_PLAIN, ec, c->stream);
+        mp::launch_fsw_blkf<T>(L.d, (const T*)L.x, (T*)L.x2, (const T*)L.b, C, h2,
+                               zero_init ? mp::FS_ZERO : ec ? mp::FS_PROLONG : mp::FS_PLAIN, ec, c->stream);
         timed_end(c, tm, words * sizeof(T) * cells);
         std::swap(L.x, L.x2);
         return;
@@ -547,7 +546,7 @@ void smooth(mp_ctx* c, int l, bool zero_init, const T* ec, bool last = false)
         std::swap(L.x, L.x2);
         return;
     }
-    if (use_blk(c, l) && L.fsw && sizeof(T) == 4) {
+    if (use_blk(c, l) && L.fsw) {
         // one pass for both colours, out of place: x read (not when zero) and
         // written, b and c read, one word each per cell; 1/8 word of coarse
         // correction after prolongation; 16 bytes per cell (phi in and out;
@@ -564,10 +563,9 @@ void smooth(mp_ctx* c, int l, bool zero_init, const T* ec, bool last = false)
             c->kev_bytes[c->kev_used / 2] = bytes;
             c->kev_used += 2;
         }
-        if constexpr (sizeof(T) == 4)
-            mp::launch_fsw_blk<T>(L.d, (const T*)L.x, (T*)L.x2, (const T*)L.b, C.cell, h2, mode, ec,
-                                  iru ? c->ir_phi : nullptr, iru ? c->ir_s : nullptr, iru && c->ir_fresh ? 1 : 0, e0,
-                                  e1, c->stream);
+        mp::launch_fsw_blk<T>(L.d, (const T*)L.x, (T*)L.x2, (const T*)L.b, C.cell, h2, mode, ec,
+                              iru ? c->ir_phi : nullptr, iru ? c->ir_s : nullptr, iru && c->ir_fresh ? 1 : 0, e0, e1,
+                              c->stream);
         std::swap(L.x, L.x2);
         return;
     }
@@ -1351,7 +1349,10 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
         c->lv[0].blk = cfg->blocked && nlev >= 2 && blocked_pays(c->d0);
         // both colours of a finest-level sweep in one pass (half the bytes of
         // two colour passes; bitwise the same), unless colour passes are asked for
-        c->lv[0].fsw = c->lv[0].blk && mx && mp::fsw_supported(c->d0) && cfg->smoother != MP_SMOOTH_PER_COLOUR;
+        auto one_pass = [&](const Dims& e) {
+            return (mx ? mp::fsw_supported(e) : mp::fsw64_supported(e)) && cfg->smoother != MP_SMOOTH_PER_COLOUR;
+        };
+        c->lv[0].fsw = c->lv[0].blk && one_pass(c->d0);
         if (c->lv[0].fsw) {
             void* p = nullptr;
             e = hipMalloc(&p, tsz * c->n0);
@@ -1362,10 +1363,11 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
         for (int l = 0; l < nlev - 1; l++) {
             Level& L = c->lv[l];
             if (c->coarse_start >= 0 && l >= c->coarse_start) break;
-            // FP32 levels only: the FP64 variants need too many registers
-            L.blkf = cfg->blocked && mx && blocked_pays(L.d);
+            // FP64: only with the one-pass sweep (the colour passes need too
+            // many registers)
+            L.blkf = cfg->blocked && blocked_pays(L.d) && (mx || one_pass(L.d));
             // both colours of a sweep in one pass
-            if (l > 0) L.fsw = L.blkf && mp::fsw_supported(L.d) && cfg->smoother != MP_SMOOTH_PER_COLOUR;
+            if (l > 0) L.fsw = L.blkf && one_pass(L.d);
             L.fused = !L.blkf && mp::sweep_supported(L.d) &&
                       (cfg->smoother == MP_SMOOTH_FUSED ||
                        (cfg->smoother == MP_SMOOTH_AUTO && L.d.n() >= kFusedMinCells));

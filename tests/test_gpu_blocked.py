@@ -235,22 +235,36 @@ def test_partly_filled_rows_equal_the_one_cell_kernels(shape, bc):
     assert np.array_equal(xa, xb)
 
 
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
 @pytest.mark.parametrize("bc", BCS)
-@pytest.mark.parametrize("shape", [(160, 64, 64), (192, 48, 32), (200, 40, 64), (100, 52, 64)])
-def test_partly_filled_rows_with_face_coefficients(shape, bc):
-    """The same kernels on stored faces: a finest level of more than 64^3 cells
-    set by the caller, by one-pass sweeps and by colour passes, bitwise through a
-    refinement step."""
-    say("partial rows, faces", shape, bc)
+@pytest.mark.parametrize("shape", [(160, 64, 64), (192, 48, 32), (200, 40, 64), (100, 52, 64), (128, 12, 8), (256, 20, 12)])
+def test_sweeps_of_a_finest_level_with_face_coefficients(shape, bc, precision):
+    """The same kernels on stored faces: a finest level set by the caller (and
+    its coarser levels), by one-pass sweeps and by colour passes, bitwise through
+    a refinement step (FP64: four cycles)."""
+    say("faces", shape, bc, precision)
     nx, ny, nz = shape
     cs = [T(c) for c in W.random_coefs(nx, ny, nz, bc, 5600)]
     rhs = T(W.random_cells(nx, ny, nz, 5700))
     out = {}
     for key, kw in (("one cell", dict(blocked=False)), ("sweep", {}), ("colours", dict(smoother="per_colour"))):
-        ctx = mproj.Context(nx, ny, nz, bc=bc, precision="mixed", max_outer=1, **kw)
+        ctx = mproj.Context(nx, ny, nz, bc=bc, precision=precision, max_outer=1, **kw)
         ctx.set_coefs(*cs)
         x, _ = ctx.solve(rhs, allow_not_converged=True)
         out[key] = N(x)
         ctx.close()
     assert np.array_equal(out["sweep"], out["one cell"])
     assert np.array_equal(out["colours"], out["one cell"])
+
+
+@pytest.mark.parametrize("bc", BCS)
+@pytest.mark.parametrize("shape,nu", [((128, 36, 32), (1, 2)), ((256, 12, 40), (2, 1)), ((200, 40, 64), (2, 2))])
+def test_fp64_one_pass_sweep_equals_colour_passes(shape, nu, bc):
+    """An odd number of sweeps per cycle leaves the iterate in the second buffer."""
+    say("fp64 sweep", shape, nu, bc)
+    p = _problem(shape, bc, 5900 + sum(shape))
+    rhs = W.random_cells(*shape, 5950 + sum(shape))
+    kw = dict(rtol=1e-11, nu1=nu[0], nu2=nu[1])
+    xa, ia = _solve(p, "fp64", True, rhs, **kw)
+    xb, ib = _solve(p, "fp64", True, rhs, smoother="per_colour", **kw)
+    assert np.array_equal(xa, xb) and ia["vcycles"] == ib["vcycles"]
