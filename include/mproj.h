@@ -99,8 +99,8 @@ typedef struct mp_config {
                                 levels whose rows of up to 512 cells (FP64:
                                 256) split into equal strips of 2, 4, 6 or 8
                                 cells over a wavefront, face-coefficient levels of >= 4M cells
-                                (tiled), and the other FP32 levels below the
-                                finest of <= 64^3 cells with even extents (one
+                                (tiled), and levels of <= 2^18 cells with even
+                                extents (one
                                 red and one black cell per thread); one launch
                                 per colour elsewhere.
                                 MP_SMOOTH_PER_COLOUR: one launch per colour on

@@ -502,6 +502,17 @@ void smooth(mp_ctx* c, int l, bool zero_init, const T* ec, bool last = false)
     const bool tm = c->cfg.kernel_timing && l == 0;
     const double cells = (double)L.d.n();
     const mp::Coef<T> C = level_coef<T>(c, l);
+    if (L.pair) {
+        // words per cell: x_old (unless zero), b, coefficients, x_new, 1/8
+        // coarse e; the red neighbours evaluated again are read from cache
+        const double words = (zero_init ? 0.0 : 1.0) + 1.0 + (C.cell ? 1.0 : 3.0) + 1.0 + (ec ? 0.125 : 0.0);
+        timed_begin(c, tm);
+        mp::launch_rb_pair<T>(L.d, (const T*)L.x, (T*)L.x2, (const T*)L.b, C, h2,
+                              zero_init ? mp::FS_ZERO : ec ? mp::FS_PROLONG : mp::FS_PLAIN, ec, c->stream);
+        timed_end(c, tm, words * sizeof(T) * cells);
+        std::swap(L.x, L.x2);
+        return;
+    }
     if (use_blkf(c, l) && L.fsw) {
         // both colours in one pass, out of place: x read (not when zero) and
         // written, b and the three faces read; 1/8 word of coarse correction
@@ -523,17 +534,6 @@ void smooth(mp_ctx* c, int l, bool zero_init, const T* ec, bool last = false)
             mp::launch_gs_blkf<T>(L.d, (T*)L.x, (const T*)L.b, C, h2, colour, mode, ec, c->stream);
             timed_end(c, tm, words * sizeof(T) * cells);
         }
-        return;
-    }
-    if (L.pair && !C.cell) {
-        // words per cell: x_old (unless zero), b, 3 coefficients, x_new, 1/8
-        // coarse e; the red neighbours evaluated again are read from cache
-        const double words = (zero_init ? 0.0 : 1.0) + 1.0 + 3.0 + 1.0 + (ec ? 0.125 : 0.0);
-        timed_begin(c, tm);
-        mp::launch_rb_pair<T>(L.d, (const T*)L.x, (T*)L.x2, (const T*)L.b, C, h2,
-                              zero_init ? mp::FS_ZERO : ec ? mp::FS_PROLONG : mp::FS_PLAIN, ec, c->stream);
-        timed_end(c, tm, words * sizeof(T) * cells);
-        std::swap(L.x, L.x2);
         return;
     }
     if (L.fused && !C.cell) {
@@ -822,7 +822,7 @@ int run_solve(mp_ctx* c, double* phi, int use_guess, mp_info* info)
         if (mx) {
             // the last V-cycle of the step applies phi += s e in its final
             // smoother pass when the finest level runs blocked kernels
-            const bool fuse_ir = use_blk(c, 0) && c->cfg.nu2 >= 1;
+            const bool fuse_ir = use_blk(c, 0) && !c->lv[0].pair && c->cfg.nu2 >= 1;
             c->ir_fresh = !phi_set;
             for (int k = 0; k < m; k++) {
                 const bool lastc = k == m - 1;
@@ -1347,10 +1347,14 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
                    (e.nx % 128 == 0 || e.n() > kPairMaxCells || cfg->smoother == MP_SMOOTH_FUSED);
         };
         c->lv[0].blk = cfg->blocked && nlev >= 2 && blocked_pays(c->d0);
-        // both colours of a finest-level sweep in one pass (half the bytes of
-        // two colour passes; bitwise the same), unless colour passes are asked for
+        // both colours of a sweep in one pass through LDS (half the bytes of two
+        // colour passes; bitwise the same), unless colour passes are asked for;
+        // small levels take the pair sweep below (128 x 64 x 32: FP64 1.3x,
+        // mixed 1.2x faster)
         auto one_pass = [&](const Dims& e) {
-            return (mx ? mp::fsw_supported(e) : mp::fsw64_supported(e)) && cfg->smoother != MP_SMOOTH_PER_COLOUR;
+            return (mx ? mp::fsw_supported(e) : mp::fsw64_supported(e)) &&
+                   (cfg->smoother == MP_SMOOTH_FUSED ||
+                    (cfg->smoother == MP_SMOOTH_AUTO && e.n() > kPairMaxCells));
         };
         c->lv[0].fsw = c->lv[0].blk && one_pass(c->d0);
         if (c->lv[0].fsw) {
@@ -1371,16 +1375,15 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
             L.fused = !L.blkf && mp::sweep_supported(L.d) &&
                       (cfg->smoother == MP_SMOOTH_FUSED ||
                        (cfg->smoother == MP_SMOOTH_AUTO && L.d.n() >= kFusedMinCells));
-            // the remaining coarser levels (below the workgroup's coarse
-            // set): both colours in one launch with the red cells around each
-            // black cell evaluated again, where a launch costs more than the
-            // level's cells.  On larger levels, and in FP64 (a true division
-            // per evaluation), the repeated evaluations cost as much as the
-            // second launch: there only when asked for (MP_SMOOTH_FUSED)
-            L.pair = l > 0 && !L.blkf && !L.fused && mp::rb_pair_supported(L.d) &&
+            // small levels: both colours in one launch with the red cells around
+            // each workgroup's box evaluated again, where a launch costs more
+            // than the level's cells.  On larger levels the repeated evaluations
+            // cost as much as the second launch: there only when asked for
+            // (MP_SMOOTH_FUSED)
+            L.pair = !L.fsw && !L.fused && mp::rb_pair_supported(L.d) &&
                      (cfg->smoother == MP_SMOOTH_FUSED ||
-                      (cfg->smoother == MP_SMOOTH_AUTO && mx && L.d.n() <= kPairMaxCells));
-            if (L.fused || L.pair || (l > 0 && L.fsw)) {
+                      (cfg->smoother == MP_SMOOTH_AUTO && L.d.n() <= kPairMaxCells));
+            if (!L.x2 && (L.fused || L.pair || L.fsw)) {
                 void* p = nullptr;
                 e = hipMalloc(&p, tsz * L.d.n());
                 good &= e == hipSuccess;

@@ -268,3 +268,29 @@ def test_fp64_one_pass_sweep_equals_colour_passes(shape, nu, bc):
     xa, ia = _solve(p, "fp64", True, rhs, **kw)
     xb, ib = _solve(p, "fp64", True, rhs, smoother="per_colour", **kw)
     assert np.array_equal(xa, xb) and ia["vcycles"] == ib["vcycles"]
+
+
+@pytest.mark.parametrize("precision", ["mixed", "fp64"])
+@pytest.mark.parametrize("bc", BCS)
+@pytest.mark.parametrize("shape", [(8, 8, 8), (4, 64, 6), (12, 10, 14), (20, 36, 6), (40, 24, 16), (130, 6, 10), (200, 4, 4)])
+def test_pair_sweep_equals_colour_passes(shape, bc, precision):
+    """Small levels (the finest included): both colours in one launch, the red
+    cells around each box of pairs evaluated again: boxes that span an axis
+    (wraps inside), partial boxes at its end, several boxes along x; cell and
+    face coefficients."""
+    say("pair sweep", shape, bc, precision)
+    nx, ny, nz = shape
+    p = _problem(shape, bc, 6100 + sum(shape))
+    cs = [T(c) for c in W.random_coefs(nx, ny, nz, bc, 6200)]
+    rhs = T(W.random_cells(nx, ny, nz, 6300))
+    out = []
+    for smoother in ("auto", "per_colour"):
+        ctx = context_for(p, precision, max_outer=1, smoother=smoother, blocked=False, coarse_cycle=False)
+        ctx.map_base_state(p.geometry, T(p.beta0_1d), T(p.rho), p.dr, p.center, want_coefs=False)
+        x, _ = ctx.solve(rhs, allow_not_converged=True)
+        ctx.set_coefs(*cs)
+        y, _ = ctx.solve(rhs, allow_not_converged=True)
+        out.append((N(x), N(y)))
+        ctx.close()
+    assert np.array_equal(out[0][0], out[1][0])
+    assert np.array_equal(out[0][1], out[1][1])
