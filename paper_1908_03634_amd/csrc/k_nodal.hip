@@ -23,7 +23,10 @@
 // Layout [mz][my][mx], x fastest; cells [nz][ny][nx].
 #include "mp_device.h"
 #include "mp_kernels.h"
+#include "mp_krylov.h"
 #include "mp_launch.h"
+
+#include <type_traits>
 
 namespace mp {
 
@@ -799,18 +802,28 @@ void launch_nd_correct(const NDims& d, double inv4h, const double* sg, const dou
 // b is made mean-zero (constants are the null space) and the residual is kept
 // mean-zero; x starts at zero, or at the x passed in when use_x0 (the
 // tolerance is then relative to the initial residual), and is returned
-// mean-zero.  Stops at ||r|| <= rtol ||r0|| or maxit.  work holds 4 n doubles.
-// WAVE: run by the first wavefront alone (n <= 64), synchronised within it
-// (the other wavefronts of the workgroup wait at a later barrier); a sum is
-// lane 0's wavefront sum either way, so both forms give the same bits.
-template <typename T, bool WAVE = false>
-__device__ void nd_block_cg(const NDims& d, const T* __restrict__ bin, T* __restrict__ xout, const T* __restrict__ sg,
-                            double inv_h12, double rtol, int maxit, int use_x0, double* __restrict__ work, double* sh,
-                            double* __restrict__ iters = nullptr)
+// mean-zero.  Stops at ||r|| <= rtol ||r0|| or maxit.
+//
+// An iteration is a serial chain of three sums and a 21-point stencil pass, so
+// latency bounds it: nodes stay with their threads (node q = tid + threads * m,
+// at most M per thread; their vectors, cell sigmas and neighbour offsets in
+// registers), only the search direction is exchanged, through ps (n doubles of
+// LDS), and a sum takes one barrier.  1024 / VJ threads, sums in the association
+// of 1024; VJ = 0: the first wavefront alone, n <= 64, synchronised within it
+// (the other wavefronts of the workgroup wait at a later barrier), the same
+// bits.  336 nodes: 1.4 us per iteration, 4.2 us with the node coordinates, the
+// offsets and the sigmas found again in every pass.
+template <typename T, int VJ, int M>
+__device__ void nd_cg(const NDims& d, const T* __restrict__ bin, T* __restrict__ xout, const T* __restrict__ sg,
+                      double inv_h12, double rtol, int maxit, int use_x0, double* ps, double (*red)[2][kWaves],
+                      double* __restrict__ iters)
 {
+    constexpr bool WAVE = VJ == 0;
+    constexpr int V = WAVE ? 1 : VJ, TH = WAVE ? kWave : 1024 / V;
+    using HT = std::conditional_t<(M > 2), T, double>;  // (registers)
     const int n = d.mx * d.my * d.mz;
     const int tid = WAVE ? (int)(threadIdx.x & (kWave - 1)) : (int)threadIdx.x;
-    const int nt = WAVE ? kWave : (int)blockDim.x;
+    int half = 0;
     auto sync = [&]() {
         if constexpr (WAVE) {
             __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
@@ -820,10 +833,171 @@ __device__ void nd_block_cg(const NDims& d, const T* __restrict__ bin, T* __rest
             __syncthreads();
         }
     };
-    auto total = [&](double v) {
-        if constexpr (WAVE) return wave_sum_bcast(v);
-        else return block_sum(v, sh);
+    auto total = [&](const double (&p)[1][V]) {
+        if constexpr (WAVE) {
+            return wave_sum_bcast(p[0][0]);
+        } else {
+            double s[1];
+            totals<V, 1>(p, s, red, half);
+            return s[0];
+        }
     };
+    // slots past the last node: sigma 0, node 0's place, values kept at 0
+    HT sig[M][8];
+    double sig4[M], x[M], r[M], ap[M];
+    int qs[M], off[M][3];
+    bool live[M];
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+        live[m] = tid + TH * m < n;
+        qs[m] = live[m] ? tid + TH * m : 0;
+        int i, j, k;
+        node_ijk(d, qs[m], i, j, k);
+        const Axis ax = axis_of(i, d.nx, d.px), ay = axis_of(j, d.ny, d.py), az = axis_of(k, d.nz, d.pz);
+        const int sy = d.mx, sz = d.mx * d.my, cy = d.nx, cz = d.nx * d.ny;
+        // neighbour offsets, 16 bits each
+        auto pack = [](int lo, int hi) { return (lo & 0xffff) | (int)((unsigned)hi << 16); };
+        off[m][0] = pack(ax.nd[0] - i, ax.nd[2] - i);
+        off[m][1] = pack((ay.nd[0] - j) * sy, (ay.nd[2] - j) * sy);
+        off[m][2] = pack((az.nd[0] - k) * sz, (az.nd[2] - k) * sz);
+        double ssig = 0.0;
+#pragma unroll
+        for (int oz = 0; oz < 2; oz++)
+#pragma unroll
+            for (int oy = 0; oy < 2; oy++)
+#pragma unroll
+                for (int ox = 0; ox < 2; ox++) {
+                    const bool ok = live[m] && ax.cok[ox] && ay.cok[oy] && az.cok[oz];
+                    const T se = ok ? sg[az.ce[oz] * cz + ay.ce[oy] * cy + ax.ce[ox]] : T(0);
+                    sig[m][4 * oz + 2 * oy + ox] = (HT)se;
+                    ssig += (double)se;
+                }
+        sig4[m] = 4.0 * ssig;
+    }
+    // ap = A y of the vector in ps; returns this thread's part of y . A y
+    auto apply = [&](double (&part)[1][V]) {
+#pragma unroll
+        for (int m = 0; m < M; m++) {
+            int o[3] = {off[m][0], off[m][1], off[m][2]};
+            // (opaque to the compiler, which would else keep every address)
+            if constexpr (M > 1) asm("" : "+v"(o[0]), "+v"(o[1]), "+v"(o[2]));
+            const int dx[2] = {(int)(short)o[0], o[0] >> 16}, dy[2] = {(int)(short)o[1], o[1] >> 16},
+                      dz[2] = {(int)(short)o[2], o[2] >> 16};
+            double ss = 0.0;
+#pragma unroll
+            for (int oz = 0; oz < 2; oz++)
+#pragma unroll
+                for (int oy = 0; oy < 2; oy++)
+#pragma unroll
+                    for (int ox = 0; ox < 2; ox++) {
+                        const int qy = qs[m] + dy[oy], qz = qs[m] + dz[oz], qyz = qz + dy[oy];
+                        const double sum = ((ps[qy + dx[ox]] + ps[qz + dx[ox]]) + ps[qyz]) + ps[qyz + dx[ox]];
+                        HT se = sig[m][4 * oz + 2 * oy + ox];
+                        if constexpr (M > 2 && sizeof(T) == 4) asm("" : "+v"(se));
+                        ss = fma((double)se, sum, ss);
+                    }
+            const double y = ps[qs[m]];
+            ap[m] = live[m] ? (sig4[m] * y - ss) * inv_h12 : 0.0;
+            part[0][m % V] = fma(live[m] ? y : 0.0, ap[m], part[0][m % V]);
+            if (M > 4 && m % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+    auto publish = [&](int m, double v) {
+        if (live[m]) ps[qs[m]] = v;
+    };
+    double pb[1][V] = {};
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+        r[m] = live[m] ? (double)bin[qs[m]] : 0.0;
+        x[m] = use_x0 && live[m] ? (double)xout[qs[m]] : 0.0;
+        pb[0][m % V] += r[m];
+        ap[m] = 0.0;
+        publish(m, x[m]);
+    }
+    const double mb = total(pb) / n;  // (its barrier also publishes x)
+    if (use_x0) {
+        if constexpr (WAVE) sync();
+        double unused[1][V] = {};
+        apply(unused);
+    }
+    double p0[1][V] = {};
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+        r[m] = live[m] ? (r[m] - mb) - ap[m] : 0.0;
+        p0[0][m % V] += r[m];
+    }
+    const double m0 = total(p0) / n;
+    double p1[1][V] = {};
+#pragma unroll
+    for (int m = 0; m < M; m++) {
+        r[m] = live[m] ? r[m] - m0 : 0.0;
+        publish(m, r[m]);
+        p1[0][m % V] = fma(r[m], r[m], p1[0][m % V]);
+    }
+    double rr = total(p1);
+    const double tol2 = rtol * rtol * rr;
+    int it = 0;
+#pragma unroll 1
+    for (; it < maxit && rr > tol2 && rr > 0.0; it++) {
+        if constexpr (WAVE) sync();
+        double pa[1][V] = {};
+        apply(pa);
+        const double pap = total(pa);
+        if (!(pap > 0.0)) break;
+        const double alpha = rr / pap;
+        double pr[1][V] = {};
+#pragma unroll
+        for (int m = 0; m < M; m++) {
+            x[m] = fma(alpha, live[m] ? ps[qs[m]] : 0.0, x[m]);
+            r[m] = fma(-alpha, ap[m], r[m]);
+            pr[0][m % V] += r[m];
+        }
+        const double mr = total(pr) / n;
+        double pq[1][V] = {};
+#pragma unroll
+        for (int m = 0; m < M; m++) {
+            r[m] = live[m] ? r[m] - mr : 0.0;
+            pq[0][m % V] = fma(r[m], r[m], pq[0][m % V]);
+        }
+        const double rr1 = total(pq);
+        const double beta = rr1 / rr;
+        rr = rr1;
+#pragma unroll
+        for (int m = 0; m < M; m++) publish(m, fma(beta, ps[qs[m]], r[m]));
+        if constexpr (!WAVE) __syncthreads();
+    }
+    // iterations of this solve added to the caller's running count
+    if (iters && tid == 0) iters[0] += (double)it;
+    double px[1][V] = {};
+#pragma unroll
+    for (int m = 0; m < M; m++) px[0][m % V] += x[m];
+    const double mx = total(px) / n;
+#pragma unroll
+    for (int m = 0; m < M; m++)
+        if (live[m]) xout[qs[m]] = (T)(x[m] - mx);
+}
+
+template <typename T, int VJ, int M>
+__global__ __launch_bounds__(1024 / VJ) void k_nd_bottom(NDims d, const T* __restrict__ bin, T* __restrict__ xout,
+                                                         const T* __restrict__ sg, double inv_h12, double rtol,
+                                                         int maxit, int use_x0, double* __restrict__ iters)
+{
+    __shared__ double ps[1024 / VJ * M];
+    __shared__ double red[2][2][kWaves];
+    nd_cg<T, VJ, M>(d, bin, xout, sg, inv_h12, rtol, maxit, use_x0, ps, red, iters);
+}
+
+// The same solve for any number of nodes, vectors in global memory (work: 4 n
+// doubles).
+template <typename T>
+__device__ void nd_block_cg(const NDims& d, const T* __restrict__ bin, T* __restrict__ xout, const T* __restrict__ sg,
+                            double inv_h12, double rtol, int maxit, int use_x0, double* __restrict__ work, double* sh,
+                            double* __restrict__ iters = nullptr)
+{
+    const int n = d.mx * d.my * d.mz;
+    const int tid = (int)threadIdx.x, nt = (int)blockDim.x;
+    auto sync = [&]() { __syncthreads(); };
+    auto total = [&](double v) { return block_sum(v, sh); };
     double* x = work;
     double* r = work + n;
     double* p = work + 2 * n;
@@ -907,7 +1081,7 @@ __device__ void nd_block_cg(const NDims& d, const T* __restrict__ bin, T* __rest
 }
 
 template <typename T>
-__global__ __launch_bounds__(1024) void k_nd_bottom(NDims d, const T* __restrict__ bin, T* __restrict__ xout,
+__global__ __launch_bounds__(1024) void k_nd_bottom_any(NDims d, const T* __restrict__ bin, T* __restrict__ xout,
                                                     const T* __restrict__ sg, double inv_h12, double rtol, int maxit,
                                                     int use_x0, double* __restrict__ work, double* __restrict__ iters)
 {
@@ -920,10 +1094,18 @@ void launch_nd_bottom(const NDims& d, const T* b, T* x, const T* sg, double inv_
                       int use_x0, double* work, double* iters, hipStream_t s)
 {
     const int n = d.mx * d.my * d.mz;
-    int nt = ((n + 63) / 64) * 64;
-    if (nt > 1024) nt = 1024;
-    hipLaunchKernelGGL((k_nd_bottom<T>), dim3(1), dim3(nt), 0, s, d, b, x, sg, inv_h12, rtol, maxit, use_x0, work,
-                       iters);
+    auto go = [&](auto kernel, int vj) {
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(1024 / vj), 0, s, d, b, x, sg, inv_h12, rtol, maxit, use_x0, iters);
+    };
+    if (n <= 256) go(k_nd_bottom<T, 4, 1>, 4);
+    else if (n <= 512) go(k_nd_bottom<T, 2, 1>, 2);
+    else if (n <= 1024) go(k_nd_bottom<T, 2, 2>, 2);
+    else if (n <= 2048) go(k_nd_bottom<T, 2, 4>, 2);
+    else if (n <= 3072) go(k_nd_bottom<T, 2, 6>, 2);
+    else if (n <= 5120) go(k_nd_bottom<T, 2, 10>, 2);
+    else
+        hipLaunchKernelGGL((k_nd_bottom_any<T>), dim3(1), dim3(1024), 0, s, d, b, x, sg, inv_h12, rtol, maxit, use_x0,
+                           work, iters);
 }
 
 // ------------------------------------------------------------- coarse cycle
@@ -932,7 +1114,7 @@ void launch_nd_bottom(const NDims& d, const T* b, T* x, const T* sg, double inv_
 // array in LDS: per level the iterate, right-hand side and residual on the
 // nodes and sigma on the cells, then the FP64 work of the bottom solve.  The
 // per-node arithmetic is that of the one-launch kernels (node_sums,
-// nd_restrict_node, nd_prolong_node, nd_block_cg), so both agree bit for bit.
+// nd_restrict_node, nd_prolong_node, nd_cg), so both agree bit for bit.
 template <typename T>
 __device__ __forceinline__ long long nd_lds_off(const NdCoarseArgs<T>& a, int l)
 {
@@ -967,7 +1149,7 @@ template <typename T>
 __global__ __launch_bounds__(1024) void k_nd_coarse(NdCoarseArgs<T> a)
 {
     __shared__ T lds[kCoarseLdsBytes / sizeof(T)];
-    __shared__ double sh[16];
+    __shared__ double red[2][2][kWaves];
     const int nl = a.nlev;
     // stage sigma of every level and the right-hand side of the top level;
     // every level starts from zero
@@ -1019,15 +1201,16 @@ __global__ __launch_bounds__(1024) void k_nd_coarse(NdCoarseArgs<T> a)
         T* x = lds + nd_lds_off(a, nl - 1);
         long long wo = nd_lds_off(a, nl) * (long long)sizeof(T);
         wo = (wo + 7) / 8;  // in doubles, 8-byte aligned
-        double* work = reinterpret_cast<double*>(lds) + wo;
+        double* ps = reinterpret_cast<double*>(lds) + wo;
         // a bottom of one wavefront's nodes runs in the first wavefront alone
-        // (no workgroup barriers inside the iteration)
+        // (no workgroup barriers inside the iteration); any other has a node
+        // per thread (the levels above it leave LDS for fewer than 1024)
         if (nn <= kWave) {
             if (threadIdx.x < kWave)
-                nd_block_cg<T, true>(d, x + nn, x, x + 3 * nn, a.bottom_inv_h12, a.bottom_rtol, a.bottom_maxit, 0,
-                                     work, sh, a.bottom_iters);
+                nd_cg<T, 0, 1>(d, x + nn, x, x + 3 * nn, a.bottom_inv_h12, a.bottom_rtol, a.bottom_maxit, 0, ps, red,
+                               a.bottom_iters);
         } else {
-            nd_block_cg<T>(d, x + nn, x, x + 3 * nn, a.bottom_inv_h12, a.bottom_rtol, a.bottom_maxit, 0, work, sh,
+            nd_cg<T, 1, 1>(d, x + nn, x, x + 3 * nn, a.bottom_inv_h12, a.bottom_rtol, a.bottom_maxit, 0, ps, red,
                            a.bottom_iters);
         }
         __syncthreads();

@@ -272,3 +272,17 @@ def test_pressure_from_the_nodal_scalar(bc):
         ctx.nodal_pi(phi, float("nan"), pi=inc)
     assert e.value.code == 5
     ctx.close()
+
+
+# the bottom kernel's forms end at 256, 512, 1024, 2048, 3072 and 5120 nodes;
+# (48, 40, 56) ends its coarse cycle on 336 nodes, one per thread
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("shape,bc", [((5, 5, 6), (1, 1, 1)), ((7, 7, 7), (1, 1, 1)), ((7, 9, 9), (0, 1, 1)),
+                                      ((11, 11, 9), (1, 1, 1)), ((13, 13, 13), (1, 1, 1)), ((15, 17, 15), (0, 0, 1)),
+                                      ((17, 17, 17), (1, 1, 1)), ((48, 40, 56), (1, 1, 1))])
+def test_nodal_bottom_sizes(shape, bc, precision):
+    nx, ny, nz = shape
+    say("nodal bottom", shape, bc, precision)
+    p = W.planar_problem(nx=nx, ny=ny, nz=nz, contrast=1e3, bc=bc, seed=7800 + nx, velocity="cells")
+    info = _project_case(p, precision)
+    assert info["bottom_iters_total"] > 0
