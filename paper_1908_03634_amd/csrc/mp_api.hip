@@ -43,6 +43,53 @@ enum {
     S_BINV = 13  // 1 when the bottom grid's inverse G is usable (read by the kernels)
 };
 
+// The device arrays of a hierarchy in one allocation: arrays are announced with
+// add(), commit() allocates the sum and sets the pointers.  hipMalloc + hipFree of
+// an array of 16 MiB take 160 us together, of 512 MiB 260 us, and a hierarchy has
+// 12 to 90 arrays.  Arrays keep the alignment that their own allocation would
+// have (2 MiB from 2 MiB on, else 4 KiB).
+struct DeviceSlab {
+    struct Part {
+        void** dst;
+        size_t bytes;
+    };
+    std::vector<Part> parts;
+    void* base = nullptr;
+
+    static size_t align_of(size_t bytes) { return bytes >= (2u << 20) ? (2u << 20) : 4096; }
+    template <typename T>
+    void add(T** dst, size_t bytes)
+    {
+        parts.push_back(Part{(void**)dst, bytes > 0 ? bytes : 1});
+    }
+    bool commit()
+    {
+        size_t end = 0;
+        for (const Part& q : parts) {
+            const size_t al = align_of(q.bytes);
+            end = (end + al - 1) / al * al + q.bytes;
+        }
+        if (hipMalloc(&base, end) != hipSuccess) {
+            base = nullptr;
+            return false;
+        }
+        size_t at = 0;
+        for (const Part& q : parts) {
+            const size_t al = align_of(q.bytes);
+            at = (at + al - 1) / al * al;
+            *q.dst = (char*)base + at;
+            at += q.bytes;
+        }
+        parts.clear();
+        return true;
+    }
+    void release()
+    {
+        if (base) (void)hipFree(base);
+        base = nullptr;
+    }
+};
+
 struct Level {
     Dims d;
     double h;
@@ -52,7 +99,6 @@ struct Level {
     void* cx = nullptr;
     void* cy = nullptr;
     void* cz = nullptr;
-    bool own_x = false, own_b = false, own_c = false, own_x2 = false;
     bool fused = false;  // both colours in one launch on this level
     bool blk = false;    // register-blocked kernels (finest level, cell mode)
     bool fsw = false;    // ... with both colours of a sweep in one pass
@@ -89,13 +135,13 @@ struct NLevel {
     void* b = nullptr;
     void* r = nullptr;
     void* sig = nullptr;  // cell sigma in the V-cycle's precision
-    bool own_x = false, own_b = false, own_sig = false;
     bool col = false;    // z-marching column kernels
     bool pair = false;   // two colours per pass (out of place: x2)
     void* x2 = nullptr;
 };
 
 struct NodalState {
+    DeviceSlab mem;
     std::vector<NLevel> lv;
     double* b64 = nullptr;          // FP64 right-hand side on the finest nodes
     double* bottom_work = nullptr;  // 4 * coarsest nodes
@@ -120,6 +166,7 @@ struct mp_ctx {
     Dims d0;
     long long n0 = 0;
     hipStream_t stream = nullptr;
+    DeviceSlab mem;  // the hierarchy and the workspace
     std::vector<Level> lv;
     double *c64x = nullptr, *c64y = nullptr, *c64z = nullptr;
     double *beta0 = nullptr, *ccell = nullptr, *b64 = nullptr;
@@ -205,14 +252,6 @@ bool test_fail_alloc(const char* name)
     return v && strcmp(v, name) == 0;
 }
 
-template <typename T>
-T* dalloc(long long n, hipError_t& e)
-{
-    void* p = nullptr;
-    e = hipMalloc(&p, (size_t)(n > 0 ? n : 1) * sizeof(T));
-    return (T*)p;
-}
-
 int check_config(const mp_config* c, mp_ctx* ctx)
 {
     if (!c) return fail(ctx, MP_ERR_ARG, "config is NULL");
@@ -238,22 +277,8 @@ int check_config(const mp_config* c, mp_ctx* ctx)
 
 void free_all(mp_ctx* c)
 {
-    for (auto& L : c->lv) {
-        if (L.own_x) (void)hipFree(L.x);
-        if (L.own_x2) (void)hipFree(L.x2);
-        if (L.own_b) (void)hipFree(L.b);
-        if (L.own_c) {
-            (void)hipFree(L.cx);
-            (void)hipFree(L.cy);
-            (void)hipFree(L.cz);
-        }
-    }
     c->lv.clear();
-    double* bufs[] = {c->c64x,     c->c64y,   c->c64z,  c->beta0,       c->ccell,
-                      c->b64,      c->partials, c->dscal, c->bottom_work, c->ginv};
-    for (double* p : bufs)
-        if (p) (void)hipFree(p);
-    if (c->ccell32) (void)hipFree(c->ccell32);
+    c->mem.release();
     if (c->sbar) (void)hipFree(c->sbar);
     if (c->scanw) (void)hipFree(c->scanw);
     double* radbufs[] = {(double*)c->rad_offs, (double*)c->rad_list, c->fold, c->avg_irr, c->seff};
@@ -274,16 +299,7 @@ void free_all(mp_ctx* c)
         if (e) (void)hipEventDestroy(e);
     c->kev.clear();
     if (c->nd) {
-        for (auto& L : c->nd->lv) {
-            if (L.own_x) (void)hipFree(L.x);
-            if (L.x2) (void)hipFree(L.x2);
-            if (L.own_b) (void)hipFree(L.b);
-            (void)hipFree(L.r);
-            if (L.own_sig) (void)hipFree(L.sig);
-        }
-        if (c->nd->b64) (void)hipFree(c->nd->b64);
-        if (c->nd->bottom_work) (void)hipFree(c->nd->bottom_work);
-        if (c->nd->partials) (void)hipFree(c->nd->partials);
+        c->nd->mem.release();
         delete c->nd;
         c->nd = nullptr;
     }
@@ -845,9 +861,9 @@ int run_solve(mp_ctx* c, double* phi, int use_guess, mp_info* info)
                 vc++;
                 // out-of-place sweeps may leave the iterate in the second buffer
                 if (c->lv[0].x != (void*)phi) {
-                    HIPCHK(c,
-                           hipMemcpyAsync(phi, c->lv[0].x, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream));
                     std::swap(c->lv[0].x, c->lv[0].x2);
+                    HIPCHK(c,
+                           hipMemcpyAsync(phi, c->lv[0].x2, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream));
                 }
             }
         }
@@ -879,15 +895,6 @@ int nd_setup(mp_ctx* c)
     c->nd = N;
     const bool mx = mixed(c);
     const size_t tsz = mx ? sizeof(float) : sizeof(double);
-    bool good = true;
-    auto alloc = [&](size_t bytes) {
-        void* p = nullptr;
-        if (hipMalloc(&p, bytes > 0 ? bytes : 1) != hipSuccess) {
-            good = false;
-            return (void*)nullptr;
-        }
-        return p;
-    };
     Dims d = c->d0;
     double h = c->cfg.h;
     for (int l = 0;; l++) {
@@ -895,19 +902,8 @@ int nd_setup(mp_ctx* c)
         L.d = node_dims(d);
         L.h = h;
         L.nn = (long long)L.d.mx * L.d.my * L.d.mz;
-        if (mx || l > 0) {
-            L.x = alloc(tsz * L.nn);
-            L.b = alloc(tsz * L.nn);
-            L.own_x = L.own_b = true;
-        }
-        L.r = alloc(tsz * L.nn);
-        if (mx || l > 0) {
-            L.sig = alloc(tsz * d.n());
-            L.own_sig = true;
-        }
         L.col = c->cfg.blocked && mp::nd_col_supported(L.d);
         L.pair = mx && L.col && mp::nd_pair_supported(L.d) && c->cfg.smoother != MP_SMOOTH_PER_COLOUR;
-        if (L.pair) L.x2 = alloc(tsz * L.nn);
         N->lv.push_back(L);
         if (!can_coarsen(d.nx, d.ny, d.nz)) break;
         d = Dims{d.nx / 2, d.ny / 2, d.nz / 2, d.px, d.py, d.pz};
@@ -915,10 +911,22 @@ int nd_setup(mp_ctx* c)
     }
     {
         const int np1 = mp::red_blocks(N->lv[0].nn), np2 = mp::nd_col_reduce_blocks(N->lv[0].d);
-        N->partials = (double*)alloc(sizeof(double) * (np1 > np2 ? np1 : np2));
+        N->mem.add(&N->partials, sizeof(double) * (np1 > np2 ? np1 : np2));
     }
-    N->b64 = (double*)alloc(sizeof(double) * N->lv[0].nn);
-    if (!mx) N->lv[0].b = N->b64;
+    d = c->d0;
+    for (int l = 0; l < (int)N->lv.size(); l++) {
+        NLevel& L = N->lv[l];
+        if (mx || l > 0) {
+            N->mem.add(&L.x, tsz * L.nn);
+            N->mem.add(&L.b, tsz * L.nn);
+            N->mem.add(&L.sig, tsz * d.n());
+        }
+        N->mem.add(&L.r, tsz * L.nn);
+        if (L.pair) N->mem.add(&L.x2, tsz * L.nn);
+        d = Dims{d.nx / 2, d.ny / 2, d.nz / 2, d.px, d.py, d.pz};
+    }
+    N->mem.add(&N->b64, sizeof(double) * N->lv[0].nn);
+    N->mem.add(&N->bottom_work, sizeof(double) * 4 * N->lv.back().nn);
     // single-workgroup coarse cycle: the trailing levels whose arrays fit LDS
     if (c->cfg.coarse_cycle) {
         const int nlev = (int)N->lv.size();
@@ -933,12 +941,14 @@ int nd_setup(mp_ctx* c)
         while (lc > 1 && fits(lc - 1)) lc--;
         N->coarse_start = (nlev >= 3 && fits(lc) && lc < nlev - 1) ? lc : -1;
     }
-    N->bottom_work = (double*)alloc(sizeof(double) * 4 * N->lv.back().nn);
     N->nb = mp::red_blocks(N->lv[0].nn);
-    if (!good) {
+    if (!N->mem.commit()) {
         (void)hipGetLastError();
+        delete N;
+        c->nd = nullptr;
         return fail(c, MP_ERR_NOMEM, "no device memory for the nodal hierarchy");
     }
+    if (!mx) N->lv[0].b = N->b64;
     return MP_OK;
 }
 
@@ -1254,16 +1264,10 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
     c->nm = radius_count(c->d0);
     const bool mx = mixed(c);
     const size_t tsz = mx ? sizeof(float) : sizeof(double);
-    hipError_t e = hipSuccess;
-    auto ok = [&](void* p) { return p != nullptr && e == hipSuccess; };
     bool good = true;
-    c->c64x = dalloc<double>(c->n0, e), good &= ok(c->c64x);
-    c->c64y = dalloc<double>(c->n0, e), good &= ok(c->c64y);
-    c->c64z = dalloc<double>(c->n0, e), good &= ok(c->c64z);
-    c->beta0 = dalloc<double>(c->n0, e), good &= ok(c->beta0);
-    c->ccell = dalloc<double>(c->n0, e), good &= ok(c->ccell);
-    c->b64 = dalloc<double>(c->n0, e), good &= ok(c->b64);
-    if (mx) c->ccell32 = dalloc<float>(c->n0, e), good &= ok(c->ccell32);
+    auto doubles = [&](double** dst, long long n) { c->mem.add(dst, sizeof(double) * (size_t)n); };
+    for (double** q : {&c->c64x, &c->c64y, &c->c64z, &c->beta0, &c->ccell, &c->b64}) doubles(q, c->n0);
+    if (mx) c->mem.add(&c->ccell32, sizeof(float) * (size_t)c->n0);
     c->nbz = mp::zred_blocks(c->d0);
     {
         int np = c->nbz > mp::kMaxRedBlocks ? c->nbz : mp::kMaxRedBlocks;
@@ -1273,10 +1277,10 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
             np = 2 * mp::proj_blk_reduce_blocks(c->d0);
         // and so does the one-cell right-hand side (b, b^2 per z-column block)
         if (2 * c->nbz > np) np = 2 * c->nbz;
-        c->partials = dalloc<double>(np, e), good &= ok(c->partials);
+        doubles(&c->partials, np);
         c->npartials = np;
     }
-    c->dscal = dalloc<double>(kScal, e), good &= ok(c->dscal);
+    doubles(&c->dscal, kScal);
     // levels
     Dims d = c->d0;
     double h = cfg->h;
@@ -1284,43 +1288,14 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
         Level L;
         L.d = d;
         L.h = h;
-        if (mx || l > 0) {
-            void* p = nullptr;
-            e = hipMalloc(&p, tsz * d.n());
-            good &= e == hipSuccess;
-            L.x = p;
-            L.own_x = true;
-            p = nullptr;
-            e = hipMalloc(&p, tsz * d.n());
-            good &= e == hipSuccess;
-            L.b = p;
-            L.own_b = true;
-        } else {
-            L.b = c->b64;
-        }
-        if (mx || l > 0) {
-            void* p[3] = {nullptr, nullptr, nullptr};
-            for (int a = 0; a < 3; a++) {
-                e = hipMalloc(&p[a], tsz * d.n());
-                good &= e == hipSuccess;
-            }
-            L.cx = p[0];
-            L.cy = p[1];
-            L.cz = p[2];
-            L.own_c = true;
-        } else {
-            L.cx = c->c64x;
-            L.cy = c->c64y;
-            L.cz = c->c64z;
-        }
         c->lv.push_back(L);
         if (!mac_can_coarsen(d.nx, d.ny, d.nz)) break;
         d = Dims{d.nx / 2, d.ny / 2, d.nz / 2, d.px, d.py, d.pz};
         h *= 2.0;
     }
-    c->bottom_work = dalloc<double>(mp::kBottomWork * c->lv.back().d.n(), e), good &= ok(c->bottom_work);
+    doubles(&c->bottom_work, mp::kBottomWork * c->lv.back().d.n());
     if (c->lv.back().d.n() <= mp::kDirectBottomCells)
-        c->ginv = dalloc<double>(mp::kDirectBottomCells * mp::kDirectBottomCells, e), good &= ok(c->ginv);
+        doubles(&c->ginv, mp::kDirectBottomCells * mp::kDirectBottomCells);
     // single-workgroup coarse cycle: trailing levels of <= kCoarseCells cells,
     // when the bottom fits one wavefront and there is more than one level
     {
@@ -1357,13 +1332,6 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
                     (cfg->smoother == MP_SMOOTH_AUTO && e.n() > kPairMaxCells));
         };
         c->lv[0].fsw = c->lv[0].blk && one_pass(c->d0);
-        if (c->lv[0].fsw) {
-            void* p = nullptr;
-            e = hipMalloc(&p, tsz * c->n0);
-            good &= e == hipSuccess;
-            c->lv[0].x2 = p;
-            c->lv[0].own_x2 = true;
-        }
         for (int l = 0; l < nlev - 1; l++) {
             Level& L = c->lv[l];
             if (c->coarse_start >= 0 && l >= c->coarse_start) break;
@@ -1383,14 +1351,20 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
             L.pair = !L.fsw && !L.fused && mp::rb_pair_supported(L.d) &&
                      (cfg->smoother == MP_SMOOTH_FUSED ||
                       (cfg->smoother == MP_SMOOTH_AUTO && L.d.n() <= kPairMaxCells));
-            if (!L.x2 && (L.fused || L.pair || L.fsw)) {
-                void* p = nullptr;
-                e = hipMalloc(&p, tsz * L.d.n());
-                good &= e == hipSuccess;
-                L.x2 = p;
-                L.own_x2 = true;
-            }
         }
+    }
+    for (int l = 0; l < (int)c->lv.size(); l++) {
+        Level& L = c->lv[l];
+        if (mx || l > 0)
+            for (void** q : {&L.x, &L.b, &L.cx, &L.cy, &L.cz}) c->mem.add(q, tsz * L.d.n());
+        if (L.fused || L.pair || L.fsw) c->mem.add(&L.x2, tsz * L.d.n());
+    }
+    good = c->mem.commit();
+    if (!mx) {
+        c->lv[0].b = c->b64;
+        c->lv[0].cx = c->c64x;
+        c->lv[0].cy = c->c64y;
+        c->lv[0].cz = c->c64z;
     }
     if (good && hipHostMalloc((void**)&c->hscal, sizeof(double) * kScal, hipHostMallocDefault) != hipSuccess)
         good = false;
