@@ -935,7 +935,8 @@ int nd_setup(mp_ctx* c)
         auto fits = [&](int from) {
             const long long b = mx ? mp::nd_coarse_lds_bytes<float>(dims.data() + from, nlev - from)
                                    : mp::nd_coarse_lds_bytes<double>(dims.data() + from, nlev - from);
-            return nlev - from <= mp::kMaxCoarse && b <= mp::kCoarseLdsBytes;
+            // (its bottom solve has a node per thread)
+            return nlev - from <= mp::kMaxCoarse && b <= mp::kCoarseLdsBytes && N->lv.back().nn <= 1024;
         };
         int lc = nlev - 1;
         while (lc > 1 && fits(lc - 1)) lc--;

@@ -286,3 +286,39 @@ def test_nodal_bottom_sizes(shape, bc, precision):
     p = W.planar_problem(nx=nx, ny=ny, nz=nz, contrast=1e3, bc=bc, seed=7800 + nx, velocity="cells")
     info = _project_case(p, precision)
     assert info["bottom_iters_total"] > 0
+
+
+# two levels in the coarse cycle would leave 1035 nodes to the bottom solve that
+# has a node per thread of 1024: these levels keep their own launches
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_nodal_bottom_too_large_for_the_coarse_cycle(precision):
+    say("nodal coarse cycle, long bottom", precision)
+    p = W.planar_problem(nx=8, ny=8, nz=456, contrast=1e2, bc=(1, 1, 1), seed=7890, velocity="cells")
+    outs = []
+    for cc in (True, False):
+        ctx = _mapped(p, precision, rtol=1e-10, coarse_cycle=cc)
+        phi, info = ctx.nodal_project(T(p.ux), T(p.uy), T(p.uz), T(p.S))
+        assert info["rel_resid"] <= 1e-10
+        outs.append(N(phi))
+        ctx.close()
+    assert np.array_equal(outs[0], outs[1])
+
+
+# nodes of a colour on the largest level of the coarse cycle: 1025 (one past a
+# place per thread), 1377, 2125 (past two), and 595 on odd extents.  h = 1 / nz:
+# 12 h^2, formed in another order inside the cycle, rounds alike on these nz
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("shape,bc", [((16, 16, 80), (1, 1, 1)), ((32, 32, 32), (1, 1, 1)), ((16, 16, 168), (1, 1, 1)),
+                                      ((24, 20, 32), (1, 0, 1))])
+def test_nodal_coarse_cycle_forms(shape, bc, precision):
+    nx, ny, nz = shape
+    say("nodal coarse cycle forms", shape, bc, precision)
+    p = W.planar_problem(nx=nx, ny=ny, nz=nz, contrast=1e3, bc=bc, seed=7950 + nz, velocity="cells")
+    outs = []
+    for cc in (True, False):
+        ctx = _mapped(p, precision, rtol=1e-10, coarse_cycle=cc)
+        ux = T(p.ux)
+        phi, _ = ctx.nodal_project(ux, T(p.uy), T(p.uz), T(p.S))
+        outs.append((N(phi), N(ux)))
+        ctx.close()
+    assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
