@@ -876,6 +876,8 @@ __device__ void nd_cg(const NDims& d, const T* __restrict__ bin, T* __restrict__
     }
     // ap = A y of the vector in ps; returns this thread's part of y . A y
     auto apply = [&](double (&part)[1][V]) {
+        // (a wavefront without nodes has no part in it)
+        if (VJ == 1 && __builtin_amdgcn_readfirstlane(tid) >= n) return;
 #pragma unroll
         for (int m = 0; m < M; m++) {
             int o[3] = {off[m][0], off[m][1], off[m][2]};
@@ -1114,7 +1116,8 @@ void launch_nd_bottom(const NDims& d, const T* b, T* x, const T* sg, double inv_
 // array in LDS: per level the iterate, right-hand side and residual on the
 // nodes and sigma on the cells, then the FP64 work of the bottom solve.  The
 // per-node arithmetic is that of the one-launch kernels (node_sums,
-// nd_restrict_node, nd_prolong_node, nd_cg), so both agree bit for bit.
+// nd_restrict_node, nd_prolong_node, nd_cg), so both agree bit for bit where
+// 12 h^2 rounds alike (formed as 12 h h here).
 template <typename T>
 __device__ __forceinline__ long long nd_lds_off(const NdCoarseArgs<T>& a, int l)
 {
@@ -1126,6 +1129,136 @@ __device__ __forceinline__ long long nd_lds_off(const NdCoarseArgs<T>& a, int l)
     return off;
 }
 
+// The four nodes (2 ti + {0, 1}, 2 tj + {0, 1}, k) of place e of a coarse-cycle
+// level, one of each colour, with what does not change between its passes: the
+// 3 x 3 x 2 cell sigmas around them (0 beyond a wall) and the neighbour offsets
+// (16 bits each; a missing neighbour is the node itself and meets sigma 0 only).
+template <typename T>
+struct NdOwn {
+    T sg[2][3][3];
+    int q0, dz, dy[2], dx[2];
+    bool on[4];
+
+    __device__ __forceinline__ static int pack(int lo, int hi) { return (lo & 0xffff) | (int)((unsigned)hi << 16); }
+
+    __device__ __forceinline__ void init(const NDims& d, const T* sig, int e)
+    {
+        const int ni = (d.mx + 1) / 2, nj = (d.my + 1) / 2;
+        const FastDiv fi((unsigned)ni), fj((unsigned)nj);
+        const bool live = e < ni * nj * d.mz;
+        int ti, tj, k;
+        split3(live ? (unsigned)e : 0u, fi, fj, ti, tj, k);
+        const int i = 2 * ti, j = 2 * tj, cy = d.nx, cz = d.nx * d.ny;
+        const Axis ax = axis_of(i, d.nx, d.px), ay = axis_of(j, d.ny, d.py), az = axis_of(k, d.nz, d.pz);
+        const Axis ax1 = axis_of(i + 1, d.nx, d.px), ay1 = axis_of(j + 1, d.ny, d.py);
+        q0 = (k * d.my + j) * d.mx + i;
+        dz = pack((az.nd[0] - k) * d.mx * d.my, (az.nd[2] - k) * d.mx * d.my);
+        dy[0] = pack((ay.nd[0] - j) * d.mx, (ay.nd[2] - j) * d.mx);
+        dy[1] = pack((ay1.nd[0] - j - 1) * d.mx, (ay1.nd[2] - j - 1) * d.mx);
+        dx[0] = pack(ax.nd[0] - i, ax.nd[2] - i);
+        dx[1] = pack(ax1.nd[0] - i - 1, ax1.nd[2] - i - 1);
+#pragma unroll
+        for (int c = 0; c < 4; c++) on[c] = live && i + (c & 1) < d.mx && j + (c >> 1) < d.my;
+        // cells i-1, i, i+1 (and so along y) and k-1, k
+        const int cxi[3] = {ax.ce[0], ax.ce[1], i + 1}, cyi[3] = {ay.ce[0], ay.ce[1], j + 1};
+        const bool cxo[3] = {ax.cok[0], ax.cok[1], i + 1 < d.nx}, cyo[3] = {ay.cok[0], ay.cok[1], j + 1 < d.ny};
+#pragma unroll
+        for (int c = 0; c < 2; c++)
+#pragma unroll
+            for (int b = 0; b < 3; b++)
+#pragma unroll
+                for (int g = 0; g < 3; g++) {
+                    const bool ok = live && cxo[g] && cyo[b] && az.cok[c];
+                    sg[c][b][g] = ok ? sig[az.ce[c] * cz + cyi[b] * cy + cxi[g]] : T(0);
+                }
+    }
+
+    // node of colour C and its stencil sums (the order of node_sums)
+    template <int C>
+    __device__ __forceinline__ int sums(int mx, const T* x, T& s1, T& s2) const
+    {
+        constexpr int cx = C & 1, cy = C >> 1;
+        int q = q0 + cx + cy * mx, px = dx[cx], py = dy[cy], pz = dz;
+        // (opaque to the compiler, which would else keep the addresses of every pass)
+        asm("" : "+v"(q), "+v"(px), "+v"(py), "+v"(pz));
+        const int ex[2] = {(int)(short)px, px >> 16}, ey[2] = {(int)(short)py, py >> 16},
+                  ez[2] = {(int)(short)pz, pz >> 16};
+        s1 = T(0);
+        s2 = T(0);
+#pragma unroll
+        for (int oz = 0; oz < 2; oz++)
+#pragma unroll
+            for (int oy = 0; oy < 2; oy++)
+#pragma unroll
+                for (int ox = 0; ox < 2; ox++) {
+                    const int qy = q + ey[oy], qz = q + ez[oz], qyz = qz + ey[oy];
+                    const T sum = ((x[qy + ex[ox]] + x[qz + ex[ox]]) + x[qyz]) + x[qyz + ex[ox]];
+                    const T se = sg[oz][oy + cy][ox + cx];
+                    s1 += se;
+                    s2 = fma(se, sum, s2);
+                }
+        return q;
+    }
+
+    template <int C>
+    __device__ __forceinline__ void gs(int mx, T* x, const T* b, T h12) const
+    {
+        if (!on[C]) return;
+        T ssig, ss;
+        const int q = sums<C>(mx, x, ssig, ss);
+        x[q] = (ss + h12 * b[q]) / (T(4) * ssig);
+    }
+
+    template <int C>
+    __device__ __forceinline__ void resid(int mx, const T* x, const T* b, T inv_h12, T* r) const
+    {
+        if (!on[C]) return;
+        T ssig, ss;
+        const int q = sums<C>(mx, x, ssig, ss);
+        r[q] = b[q] - (T(4) * ssig * x[q] - ss) * inv_h12;
+    }
+};
+
+// `sweeps` sweeps on one level, down (colours 0 to 3, then r = b - A x) or up
+// (3 to 0), with M places (NdOwn) per thread.  In one workgroup a pass is bound
+// by the instructions that its wavefronts issue, and most of those found
+// coordinates, neighbours and sigmas again.  Cycle on 16 x 16 x 17 nodes and
+// below, FP32: 88 us, 140 us before; 13 x 11 x 15 and 7 x 6 x 8, FP64: 197, 218 us.
+template <typename T, int M>
+__device__ __forceinline__ void nd_cc_smooth(const NDims& d, T* x, const T* b, const T* sg, T h12, T inv_h12, T* r,
+                                             int sweeps, bool down)
+{
+    const int mx = d.mx;
+    NdOwn<T> o0, o1;
+    o0.init(d, sg, (int)threadIdx.x);
+    if constexpr (M == 2) o1.init(d, sg, (int)threadIdx.x + 1024);
+    auto gs = [&](auto colour) {
+        constexpr int C = decltype(colour)::value;
+        o0.template gs<C>(mx, x, b, h12);
+        if constexpr (M == 2) o1.template gs<C>(mx, x, b, h12);
+        __syncthreads();
+    };
+    auto resid = [&](auto colour) {
+        constexpr int C = decltype(colour)::value;
+        o0.template resid<C>(mx, x, b, inv_h12, r);
+        if constexpr (M == 2) o1.template resid<C>(mx, x, b, inv_h12, r);
+    };
+    using C0 = std::integral_constant<int, 0>;
+    using C1 = std::integral_constant<int, 1>;
+    using C2 = std::integral_constant<int, 2>;
+    using C3 = std::integral_constant<int, 3>;
+#pragma unroll 1
+    for (int s = 0; s < sweeps; s++) {
+        if (down) gs(C0{}), gs(C1{}), gs(C2{}), gs(C3{});
+        else gs(C3{}), gs(C2{}), gs(C1{}), gs(C0{});
+    }
+    if (down) {
+        resid(C0{}), resid(C1{}), resid(C2{}), resid(C3{});
+        __syncthreads();
+    }
+}
+
+// The same for levels of more than 2048 nodes of a colour.
 template <typename T>
 __device__ __forceinline__ void nd_cc_gs(const NDims& d, T* x, const T* b, const T* sg, T h12, int colour)
 {
@@ -1146,6 +1279,32 @@ __device__ __forceinline__ void nd_cc_gs(const NDims& d, T* x, const T* b, const
 }
 
 template <typename T>
+__device__ __forceinline__ void nd_cc_level(const NDims& d, T* x, const T* b, const T* sg, T h12, T inv_h12, T* r,
+                                            int sweeps, bool down)
+{
+    const int cnt = ((d.mx + 1) / 2) * ((d.my + 1) / 2) * d.mz;
+    if (cnt <= 1024) {
+        nd_cc_smooth<T, 1>(d, x, b, sg, h12, inv_h12, r, sweeps, down);
+    } else if (sizeof(T) == 4 && cnt <= 2048) {
+        nd_cc_smooth<T, 2>(d, x, b, sg, h12, inv_h12, r, sweeps, down);
+    } else {
+        for (int s = 0; s < sweeps; s++)
+            for (int c = 0; c < 4; c++) nd_cc_gs<T>(d, x, b, sg, h12, down ? c : 3 - c);
+        if (!down) return;
+        const int nn = d.mx * d.my * d.mz;
+        const FastDiv fx((unsigned)d.mx), fy((unsigned)d.my);
+        for (int e = threadIdx.x; e < nn; e += blockDim.x) {
+            int i, j, k;
+            split3((unsigned)e, fx, fy, i, j, k);
+            T ssig, ss;
+            node_sums<T>(d, x, sg, i, j, k, ssig, ss);
+            r[e] = b[e] - (T(4) * ssig * x[e] - ss) * inv_h12;
+        }
+        __syncthreads();
+    }
+}
+
+template <typename T>
 __global__ __launch_bounds__(1024) void k_nd_coarse(NdCoarseArgs<T> a)
 {
     __shared__ T lds[kCoarseLdsBytes / sizeof(T)];
@@ -1154,7 +1313,7 @@ __global__ __launch_bounds__(1024) void k_nd_coarse(NdCoarseArgs<T> a)
     // stage sigma of every level and the right-hand side of the top level;
     // every level starts from zero
     for (int l = 0; l < nl; l++) {
-        const NDims& d = a.lv[l].d;
+        const NDims d = a.lv[l].d;
         const int nn = d.mx * d.my * d.mz, nc = d.nx * d.ny * d.nz;
         T* base = lds + nd_lds_off(a, l);
         for (int e = threadIdx.x; e < nn; e += blockDim.x) {
@@ -1166,24 +1325,14 @@ __global__ __launch_bounds__(1024) void k_nd_coarse(NdCoarseArgs<T> a)
     __syncthreads();
     // down
     for (int l = 0; l < nl - 1; l++) {
-        const NDims& d = a.lv[l].d;
+        const NDims d = a.lv[l].d;
         const int nn = d.mx * d.my * d.mz;
         T* x = lds + nd_lds_off(a, l);
         T* b = x + nn;
         T* r = b + nn;
         const T* sg = r + nn;
-        for (int s = 0; s < a.nu1; s++)
-            for (int colour = 0; colour < 4; colour++) nd_cc_gs<T>(d, x, b, sg, a.lv[l].h12, colour);
-        const FastDiv fx((unsigned)d.mx), fy((unsigned)d.my);
-        for (int e = threadIdx.x; e < nn; e += blockDim.x) {
-            int i, j, k;
-            split3((unsigned)e, fx, fy, i, j, k);
-            T ssig, ss;
-            node_sums<T>(d, x, sg, i, j, k, ssig, ss);
-            r[e] = b[e] - (T(4) * ssig * x[e] - ss) * a.lv[l].inv_h12;
-        }
-        __syncthreads();
-        const NDims& c = a.lv[l + 1].d;
+        nd_cc_level<T>(d, x, b, sg, a.lv[l].h12, a.lv[l].inv_h12, r, a.nu1, true);
+        const NDims c = a.lv[l + 1].d;
         const int nnc = c.mx * c.my * c.mz;
         T* bc = lds + nd_lds_off(a, l + 1) + nnc;
         const FastDiv fxc((unsigned)c.mx), fyc((unsigned)c.my);
@@ -1196,7 +1345,7 @@ __global__ __launch_bounds__(1024) void k_nd_coarse(NdCoarseArgs<T> a)
     }
     // bottom: FP64 conjugate gradients by the whole workgroup, work in LDS
     {
-        const NDims& d = a.lv[nl - 1].d;
+        const NDims d = a.lv[nl - 1].d;
         const int nn = d.mx * d.my * d.mz;
         T* x = lds + nd_lds_off(a, nl - 1);
         long long wo = nd_lds_off(a, nl) * (long long)sizeof(T);
@@ -1204,7 +1353,7 @@ __global__ __launch_bounds__(1024) void k_nd_coarse(NdCoarseArgs<T> a)
         double* ps = reinterpret_cast<double*>(lds) + wo;
         // a bottom of one wavefront's nodes runs in the first wavefront alone
         // (no workgroup barriers inside the iteration); any other has a node
-        // per thread (the levels above it leave LDS for fewer than 1024)
+        // per thread (larger bottoms have no coarse cycle)
         if (nn <= kWave) {
             if (threadIdx.x < kWave)
                 nd_cg<T, 0, 1>(d, x + nn, x, x + 3 * nn, a.bottom_inv_h12, a.bottom_rtol, a.bottom_maxit, 0, ps, red,
@@ -1217,24 +1366,24 @@ __global__ __launch_bounds__(1024) void k_nd_coarse(NdCoarseArgs<T> a)
     }
     // up
     for (int l = nl - 2; l >= 0; l--) {
-        const NDims& d = a.lv[l].d;
+        const NDims d = a.lv[l].d;
         const int nn = d.mx * d.my * d.mz;
         T* x = lds + nd_lds_off(a, l);
         const T* b = x + nn;
         const T* sg = x + 3 * nn;
+        const NDims c = a.lv[l + 1].d;
         const T* xc = lds + nd_lds_off(a, l + 1);
         const FastDiv fx((unsigned)d.mx), fy((unsigned)d.my);
         for (int e = threadIdx.x; e < nn; e += blockDim.x) {
             int i, j, k;
             split3((unsigned)e, fx, fy, i, j, k);
-            x[e] += nd_prolong_node<T>(a.lv[l + 1].d, xc, i, j, k);
+            x[e] += nd_prolong_node<T>(c, xc, i, j, k);
         }
         __syncthreads();
-        for (int s = 0; s < a.nu2; s++)
-            for (int colour = 3; colour >= 0; colour--) nd_cc_gs<T>(d, x, b, sg, a.lv[l].h12, colour);
+        nd_cc_level<T>(d, x, b, sg, a.lv[l].h12, a.lv[l].inv_h12, x, a.nu2, false);
     }
     {
-        const NDims& d = a.lv[0].d;
+        const NDims d = a.lv[0].d;
         const int nn = d.mx * d.my * d.mz;
         const T* x = lds;
         for (int e = threadIdx.x; e < nn; e += blockDim.x) a.lv[0].x[e] = x[e];
