@@ -460,6 +460,115 @@ template void launch_nd_resid_col<float>(const NDims&, const float*, const float
 template void launch_nd_resid_col<double>(const NDims&, const double*, const double*, const double*, double,
                                           double*, hipStream_t);
 
+// ------------------------------------------------------------- two colours per pass
+
+// Both colours of the rows of one parity in one launch, for any node grid (out
+// of place, with the operands of k_nd_pair: own rows from xo, rows of the other
+// parity from xnb, the updated rows to xn).  A node of the second colour meets
+// the first colour only in its own row, one node along x and one plane along z,
+// so a workgroup takes up to 64 pairs of a row in tz planes: it updates the
+// first colour there and on the pair and the planes next to them (recomputed,
+// not stored) into LDS, then the second colour.  Operands and order of
+// node_sums: the same bits as two colour launches.
+// Launches and the latency of the load chain bound a colour pass on these grids:
+// one node per thread leaves two loads in a row per pass, and the grid is cut to
+// 512 workgroups or planes of 2.  25 x 21 x 29 nodes FP64: 4.6 us for two
+// colours, 11 us as column launches; 97 x 81 x 113: 14.7 us, 19 us.
+constexpr int kNpaPairs = 64;   // pairs of a row per workgroup, at most (rows are cut evenly)
+constexpr int kNpaPlanes = 16;  // planes, at most
+
+template <typename T>
+__global__ __launch_bounds__(256) void k_nd_pair_any(NDims d, int tz, int tw, const T* __restrict__ xo,
+                                                     const T* __restrict__ xnb, T* __restrict__ xn,
+                                                     const T* __restrict__ b, const T* __restrict__ sg, T h12,
+                                                     int rowpar, int lead)
+{
+    __shared__ T first[(kNpaPlanes + 2) * (kNpaPairs + 1)];
+    const int nt = (d.mx + 1) / 2, t0 = (int)blockIdx.x * tw, w = min(tw, nt - t0);
+    const int j = 2 * (int)blockIdx.y + rowpar;
+    const int z0 = (int)blockIdx.z * tz, np = min(tz, d.mz - z0);
+    const Axis ay = axis_of(j, d.ny, d.py);
+    const int sz = d.mx * d.my, cz = d.nx * d.ny;
+    // node i of row j, plane k; own(c, a): value of the row at x offset a, plane offset c (0: -1, 1: +1)
+    auto update = [&](int i, int k, auto&& own) {
+        const Axis ax = axis_of(i, d.nx, d.px), az = axis_of(k, d.nz, d.pz);
+        T s1 = T(0), s2 = T(0);
+#pragma unroll
+        for (int oz = 0; oz < 2; oz++)
+#pragma unroll
+            for (int oy = 0; oy < 2; oy++) {
+                const T* rm = xnb + (az.nd[1] * sz + ay.nd[2 * oy] * d.mx);      // this plane, next row
+                const T* rz = xnb + (az.nd[2 * oz] * sz + ay.nd[2 * oy] * d.mx);  // next plane and row
+                const T* cc = sg + (az.ce[oz] * cz + ay.ce[oy] * d.nx);
+                const bool cyz = ay.cok[oy] && az.cok[oz];
+#pragma unroll
+                for (int ox = 0; ox < 2; ox++) {
+                    // (a corner that is missing belongs to a missing cell, sigma 0)
+                    const T se = cyz && ax.cok[ox] ? cc[ax.ce[ox]] : T(0);
+                    const int ii = ax.nd[2 * ox];
+                    const T sum = ((rm[ii] + own(az.nd[2 * oz], oz, ii, ox)) + rz[i]) + rz[ii];
+                    s1 += se;
+                    s2 = fma(se, sum, s2);
+                }
+            }
+        return (s2 + h12 * b[k * sz + j * d.mx + i]) / (T(4) * s1);
+    };
+    // first colour: pairs t0 .. t0 + w (lead 0) or t0 - 1 .. t0 + w - 1, planes z0 - 1 .. z0 + np
+    const int w1 = w + 1;
+    const FastDiv f1((unsigned)w1), f2((unsigned)w);
+    for (int e = threadIdx.x; e < w1 * (np + 2); e += 256) {
+        const int p = (int)f1.div((unsigned)e), u = e - p * w1;
+        int k = z0 - 1 + p, i = 2 * (t0 - lead + u) + lead;
+        const bool mine = p >= 1 && p <= np && (lead ? u >= 1 : u < w) && i < d.mx;
+        if (d.pz) k = k < 0 ? k + d.mz : (k >= d.mz ? k - d.mz : k);
+        if (d.px) i = i < 0 ? i + d.mx : (i >= d.mx ? i - d.mx : i);
+        T v = T(0);
+        if (k >= 0 && k < d.mz && i >= 0 && i < d.mx) {
+            const T* r = xo + j * d.mx;
+            v = update(i, k, [&](int kk, int, int ii, int) { return r[kk * sz + ii]; });
+            if (mine) xn[k * sz + j * d.mx + i] = v;
+        }
+        first[p * (kNpaPairs + 1) + u] = v;
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < w * np; e += 256) {
+        const int p = (int)f2.div((unsigned)e), u = e - p * w;
+        const int k = z0 + p, i = 2 * (t0 + u) + 1 - lead;
+        if (i >= d.mx) continue;
+        const T* f = first + p * (kNpaPairs + 1) + u;
+        xn[k * sz + j * d.mx + i] =
+            update(i, k, [&](int, int oz, int, int ox) { return f[2 * oz * (kNpaPairs + 1) + ox]; });
+    }
+}
+
+// Periodic rows and columns have even counts on every level that is smoothed.
+// Up to 2^22 nodes: beyond, the one-colour columns, which read each value once
+// per pass, are faster (FP64 solves: 160^3 6.04 against 6.14 ms, 192^3 9.05
+// against 8.8, 256^3 19.0 against 15.8).
+bool nd_pair_any_supported(const NDims& d)
+{
+    return (!d.px || d.mx % 2 == 0) && (!d.py || d.my % 2 == 0) && d.mx >= 2 && d.my >= 2 && d.mz >= 2 &&
+           d.my < 65536 && d.mz < 65536 && (long long)d.mx * d.my * d.mz <= (1 << 22);
+}
+
+template <typename T>
+void launch_nd_pair_any(const NDims& d, const T* xo, const T* xnb, T* xn, const T* b, const T* sg, T h12, int rowpar,
+                        int lead, hipStream_t s)
+{
+    const int nt = (d.mx + 1) / 2, rows = (d.my - rowpar + 1) / 2;
+    const int gx = (nt + kNpaPairs - 1) / kNpaPairs;
+    const long long bxy = (long long)gx * rows;
+    int tz = kNpaPlanes;
+    while (tz > 2 && bxy * ((d.mz + tz - 1) / tz) < 512) tz /= 2;
+    const dim3 grid(gx, rows, (d.mz + tz - 1) / tz);
+    hipLaunchKernelGGL((k_nd_pair_any<T>), grid, dim3(256), 0, s, d, tz, (nt + gx - 1) / gx, xo, xnb, xn, b, sg, h12, rowpar, lead);
+}
+
+template void launch_nd_pair_any<float>(const NDims&, const float*, const float*, float*, const float*, const float*,
+                                        float, int, int, hipStream_t);
+template void launch_nd_pair_any<double>(const NDims&, const double*, const double*, double*, const double*,
+                                         const double*, double, int, int, hipStream_t);
+
 // ------------------------------------------------------------- transfers
 
 // Coarse right-hand side = (1/8) P^T r at coarse node (I, J, K): the fine

@@ -136,7 +136,8 @@ struct NLevel {
     void* r = nullptr;
     void* sig = nullptr;  // cell sigma in the V-cycle's precision
     bool col = false;    // z-marching column kernels
-    bool pair = false;   // two colours per pass (out of place: x2)
+    bool pair = false;      // two colours per pass (out of place: x2)
+    bool pair_any = false;  // ... by the kernel for any node grid
     void* x2 = nullptr;
 };
 
@@ -903,7 +904,14 @@ int nd_setup(mp_ctx* c)
         L.h = h;
         L.nn = (long long)L.d.mx * L.d.my * L.d.mz;
         L.col = c->cfg.blocked && mp::nd_col_supported(L.d);
-        L.pair = mx && L.col && mp::nd_pair_supported(L.d) && c->cfg.smoother != MP_SMOOTH_PER_COLOUR;
+        if (L.col && c->cfg.smoother != MP_SMOOTH_PER_COLOUR) {
+            // whole rows per wavefront where they stream (128 x 128 x 129: 8.7 us
+            // a pass), the parallel form where latency counts (64 x 64 x 65: 5.3
+            // us, 6.9 by rows; 32 x 32 x 33: 4.6, 6.2)
+            L.pair_any = !(mx && mp::nd_pair_supported(L.d) &&
+                           (c->cfg.smoother == MP_SMOOTH_FUSED || L.nn > (1 << 19)));
+            L.pair = !L.pair_any || mp::nd_pair_any_supported(L.d);
+        }
         N->lv.push_back(L);
         if (!can_coarsen(d.nx, d.ny, d.nz)) break;
         d = Dims{d.nx / 2, d.ny / 2, d.nz / 2, d.px, d.py, d.pz};
@@ -1027,18 +1035,25 @@ void nd_vcycle(mp_ctx* c, int l)
     // a sweep as two passes of two colours (rows of one parity each), out of
     // place: the second pass reads the rows the first wrote
     auto sweep = [&](bool down) {
-        if constexpr (sizeof(T) == 4) {
-            if (L.pair) {
-                // down: colours 0, 1 (even rows, x parity 0 first), then 2, 3;
-                // up: colours 3, 2 (odd rows, x parity 1 first), then 1, 0
-                const int r0 = down ? 0 : 1, lead = down ? 0 : 1;
-                mp::launch_nd_pair<T>(L.d, (const T*)L.x, (const T*)L.x, (T*)L.x2, (const T*)L.b, (const T*)L.sig, h12,
-                                      r0, lead, c->stream);
-                mp::launch_nd_pair<T>(L.d, (const T*)L.x, (const T*)L.x2, (T*)L.x2, (const T*)L.b, (const T*)L.sig,
-                                      h12, 1 - r0, lead, c->stream);
-                std::swap(L.x, L.x2);
-                return;
-            }
+        if (L.pair) {
+            // down: colours 0, 1 (even rows, x parity 0 first), then 2, 3;
+            // up: colours 3, 2 (odd rows, x parity 1 first), then 1, 0
+            const int r0 = down ? 0 : 1, lead = down ? 0 : 1;
+            auto pass = [&](const void* other, int rowpar) {
+                if constexpr (sizeof(T) == 4) {
+                    if (!L.pair_any) {
+                        mp::launch_nd_pair<T>(L.d, (const T*)L.x, (const T*)other, (T*)L.x2, (const T*)L.b,
+                                              (const T*)L.sig, h12, rowpar, lead, c->stream);
+                        return;
+                    }
+                }
+                mp::launch_nd_pair_any<T>(L.d, (const T*)L.x, (const T*)other, (T*)L.x2, (const T*)L.b,
+                                          (const T*)L.sig, h12, rowpar, lead, c->stream);
+            };
+            pass(L.x, r0);
+            pass(L.x2, 1 - r0);
+            std::swap(L.x, L.x2);
+            return;
         }
         if (down)
             for (int colour = 0; colour < 4; colour++) gs(colour);
@@ -1148,6 +1163,11 @@ int nd_solve(mp_ctx* c, double* phi, int use_guess, mp_info* info)
                 nd_vcycle<double>(c, 0);
                 c->extra_post = 0;
                 vc++;
+                // out-of-place sweeps may leave the iterate in the second buffer
+                if (L0.x != (void*)phi) {
+                    std::swap(L0.x, L0.x2);
+                    HIPCHK(c, hipMemcpyAsync(phi, L0.x2, sizeof(double) * n, hipMemcpyDeviceToDevice, c->stream));
+                }
             }
         }
     }

@@ -322,6 +322,11 @@ bool nd_pair_supported(const NDims& d);
 template <typename T>
 void launch_nd_pair(const NDims& d, const T* xo, const T* xnb, T* xn, const T* b, const T* sg, T h12, int rowpar,
                     int lead, hipStream_t s);
+// The same for any node grid (k_nodal.hip).
+bool nd_pair_any_supported(const NDims& d);
+template <typename T>
+void launch_nd_pair_any(const NDims& d, const T* xo, const T* xnb, T* xn, const T* b, const T* sg, T h12, int rowpar,
+                        int lead, hipStream_t s);
 // r = b - A x; inv_h12 = 1 / (12 h^2).
 template <typename T>
 void launch_nd_resid(const NDims& d, const T* x, const T* b, const T* sg, T inv_h12, T* r, hipStream_t s);

@@ -322,3 +322,29 @@ def test_nodal_coarse_cycle_forms(shape, bc, precision):
         outs.append((N(phi), N(ux)))
         ctx.close()
     assert np.array_equal(outs[0][0], outs[1][0]) and np.array_equal(outs[0][1], outs[1][1])
+
+
+# two-colour passes of any node grid: rows of 2, 3, 65 and 129 pairs (64 to a
+# workgroup), one workgroup's planes and a remainder, every boundary
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("shape,bc", [((4, 4, 4), (0, 0, 0)), ((4, 4, 4), (1, 1, 1)), ((128, 8, 20), (1, 0, 1)),
+                                      ((256, 4, 8), (1, 1, 0)), ((20, 36, 132), (0, 1, 1)), ((64, 48, 36), (0, 0, 1)),
+                                      ((130, 12, 12), (0, 0, 0)), ((32, 8, 10), (0, 0, 1)), ((256, 12, 10), (0, 0, 1)),
+                                      ((160, 160, 160), (1, 1, 1))])
+def test_two_colour_passes_of_any_grid_equal_four_colour_passes(shape, bc, precision):
+    nx, ny, nz = shape
+    say("nodal pair, any grid", shape, bc, precision)
+    p = W.planar_problem(nx=nx, ny=ny, nz=nz, contrast=1e3, bc=bc, seed=7700 + nx + nz, velocity="cells")
+    outs = []
+    # an odd and an even number of sweeps per cycle (the iterate's two buffers);
+    # "fused" keeps whole rows per wavefront where it can
+    for nu2 in (1, 2):
+        for sm in ("auto", "fused", "per_colour"):
+            ctx = _mapped(p, precision, rtol=1e-9, smoother=sm, nu1=2, nu2=nu2, coarse_cycle=False)
+            ux, uz = T(p.ux), T(p.uz)
+            phi, info = ctx.nodal_project(ux, T(p.uy), uz, T(p.S))
+            outs.append((N(phi), N(ux), N(uz), info["vcycles"]))
+            ctx.close()
+        b = outs[-1]
+        for a in outs[-3:-1]:
+            assert a[3] == b[3] and all(np.array_equal(u, v) for u, v in zip(a[:3], b[:3]))
