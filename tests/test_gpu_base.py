@@ -331,3 +331,30 @@ def test_full_split_velocity_matches_the_oracle_chain(kind):
         scale = np.abs(oracle.beta0_divergence(g, ref["beta0_cc"], p.ux, p.uy, p.uz)).max()
         assert np.abs(d - want).max() <= 1e-10 * scale
     ctx.close()
+
+
+# the edge search starts from a guess (edges equal in r or in r^2): edges far from
+# both, a single edge, two edges, and edges that cover a part of the radii only
+@pytest.mark.parametrize("edges", ["geometric", "cubic", "random", "one", "two", "inner", "outer"])
+def test_add_w0_on_uneven_edges(edges):
+    say("add_w0", edges)
+    p = W.spherical_problem(32, contrast=1e3, seed=7210, base="linear")
+    rng = np.random.default_rng(7211)
+    top = p.h * 32
+    re = {"geometric": top * 1.05 ** np.arange(-300.0, 1.0), "cubic": top * (np.arange(200) / 199.0) ** 3,
+          "random": np.sort(rng.uniform(0.0, top, 777)), "one": np.array([0.3 * top]),
+          "two": np.array([0.1, 0.4]) * top, "inner": np.linspace(0.0, 0.2, 50) * top,
+          "outer": np.linspace(0.3, 0.35, 64) * top}[edges]
+    w0 = rng.standard_normal(len(re))
+    ref = oracle.add_w0(oracle.Grid.of(p), 1, w0, re, p.center, p.ux, p.uy, p.uz)
+    ctx = context_for(p, "fp64")
+    ctx.map_base_state(p.geometry, T(p.beta0_1d), T(p.rho), p.dr, p.center, want_coefs=False)
+    u = [T(p.ux), T(p.uy), T(p.uz)]
+    ctx.add_w0(T(w0), *u, re=T(re))
+    # a radius rounds within 2^-52 r, and w0's slope is at most the largest difference
+    # over its interval
+    slope = np.abs(np.diff(w0) / np.diff(re)).max() if len(re) > 1 else 0.0
+    tol = 1e-14 * max(np.abs(b).max() for b in ref) + 2.0 * slope * top * 2.0 ** -52
+    for a, b in zip(u, ref):
+        assert np.abs(N(a) - b).max() <= tol
+    ctx.close()
