@@ -929,7 +929,7 @@ int nd_setup(mp_ctx* c)
         L.col = c->cfg.blocked && mp::nd_col_supported(L.d);
         if (L.col && c->cfg.smoother != MP_SMOOTH_PER_COLOUR) {
             // whole rows per wavefront where they stream (128 x 128 x 129: 8.7 us
-            // a pass), the parallel form where latency counts (64 x 64 x 65: 5.3
+            // a pass), the parallel form where latency counts (64 x 64 x 65: 5.6
             // us, 6.9 by rows; 32 x 32 x 33: 4.6, 6.2)
             L.pair_any = !(mx && mp::nd_pair_supported(L.d) &&
                            (c->cfg.smoother == MP_SMOOTH_FUSED || L.nn > (1 << 19)));
