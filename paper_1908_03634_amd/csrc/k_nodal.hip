@@ -25,52 +25,13 @@
 #include "mp_kernels.h"
 #include "mp_krylov.h"
 #include "mp_launch.h"
+#include "mp_nodal.h"
 
 #include <type_traits>
 
 namespace mp {
 
 namespace {
-
-// Node neighbours along one axis (offsets -1, 0, +1) and the cells below and
-// above the node (offsets -1, 0).  Missing ones (beyond a wall) are flagged
-// and point at the node itself / cell 0 so every load stays in bounds.
-struct Axis {
-    int nd[3];
-    bool nok[3];
-    int ce[2];
-    bool cok[2];
-};
-
-__device__ __forceinline__ Axis axis_of(int i, int n, int per)
-{
-    Axis a;
-#pragma unroll
-    for (int o = 0; o < 3; o++) {
-        int t = i + o - 1;
-        if (per) {
-            t = t < 0 ? t + n : (t >= n ? t - n : t);
-            a.nd[o] = t;
-            a.nok[o] = true;
-        } else {
-            a.nok[o] = t >= 0 && t <= n;
-            a.nd[o] = a.nok[o] ? t : i;
-        }
-    }
-#pragma unroll
-    for (int o = 0; o < 2; o++) {
-        int t = i + o - 1;
-        if (per) {
-            t = t < 0 ? t + n : t;
-            a.ce[o] = t;
-            a.cok[o] = true;
-        } else {
-            a.cok[o] = t >= 0 && t < n;
-            a.ce[o] = a.cok[o] ? t : 0;
-        }
-    }
-    return a;
-}
 
 // Sums of the stencil at node (i,j,k) in precision T (fixed order: cells by
 // z, y, x offset; in each cell the three face-diagonal corners, then the far
@@ -488,6 +449,8 @@ __global__ __launch_bounds__(256) void k_nd_pair_any(NDims d, int tz, int tw, co
     const int j = 2 * (int)blockIdx.y + rowpar;
     const int z0 = (int)blockIdx.z * tz, np = min(tz, d.mz - z0);
     const Axis ay = axis_of(j, d.ny, d.py);
+    // rows of the other parity, beside a wall too: row j of xn is written here
+    const int jb[2] = {beside(ay, 0), beside(ay, 1)};
     const int sz = d.mx * d.my, cz = d.nx * d.ny;
     // node i of row j, plane k; own(c, a): value of the row at x offset a, plane offset c (0: -1, 1: +1)
     auto update = [&](int i, int k, auto&& own) {
@@ -497,8 +460,8 @@ __global__ __launch_bounds__(256) void k_nd_pair_any(NDims d, int tz, int tw, co
         for (int oz = 0; oz < 2; oz++)
 #pragma unroll
             for (int oy = 0; oy < 2; oy++) {
-                const T* rm = xnb + (az.nd[1] * sz + ay.nd[2 * oy] * d.mx);      // this plane, next row
-                const T* rz = xnb + (az.nd[2 * oz] * sz + ay.nd[2 * oy] * d.mx);  // next plane and row
+                const T* rm = xnb + (az.nd[1] * sz + jb[oy] * d.mx);      // this plane, next row
+                const T* rz = xnb + (az.nd[2 * oz] * sz + jb[oy] * d.mx);  // next plane and row
                 const T* cc = sg + (az.ce[oz] * cz + ay.ce[oy] * d.nx);
                 const bool cyz = ay.cok[oy] && az.cok[oz];
 #pragma unroll

@@ -348,3 +348,29 @@ def test_two_colour_passes_of_any_grid_equal_four_colour_passes(shape, bc, preci
         b = outs[-1]
         for a in outs[-3:-1]:
             assert a[3] == b[3] and all(np.array_equal(u, v) for u, v in zip(a[:3], b[:3]))
+
+
+# without pre-smoothing the first pass after the coarse correction is the first to
+# write a level's second buffer: what an earlier call left there (not a number)
+# must not reach the rows beside a wall in y
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("nu2", [1, 2])
+@pytest.mark.parametrize("bc", [(1, 1, 1), (0, 1, 0), (0, 1, 1)])
+def test_two_colour_passes_beside_walls_after_a_failed_call(bc, nu2, precision):
+    say("nodal pair, walls in y", bc, nu2, precision)
+    p = W.planar_problem(nx=16, ny=12, nz=20, contrast=1e3, bc=bc, seed=7730, velocity="cells")
+    kw = dict(rtol=1e-8, nu1=0, nu2=nu2, coarse_cycle=False)
+    ctx = context_for(p, precision, **kw)
+    # values of b / sigma that no double holds
+    ctx.map_base_state(p.geometry, T(p.beta0_1d), T(p.rho * 1e300), p.dr, p.center, want_coefs=False)
+    with pytest.raises(mproj.MprojError):
+        ctx.nodal_project(*(T(u * 1e140) for u in (p.ux, p.uy, p.uz)), T(p.S))
+    outs = []
+    for c in (ctx, context_for(p, precision, smoother="per_colour", **kw)):
+        c.map_base_state(p.geometry, T(p.beta0_1d), T(p.rho), p.dr, p.center, want_coefs=False)
+        ux = T(p.ux)
+        phi, info = c.nodal_project(ux, T(p.uy), T(p.uz), T(p.S))
+        assert info["rel_resid"] <= 1e-8
+        outs.append((N(phi), N(ux)))
+        c.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*outs))
