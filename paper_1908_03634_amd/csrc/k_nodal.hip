@@ -927,11 +927,10 @@ __device__ void nd_cg(const NDims& d, const T* __restrict__ bin, T* __restrict__
         node_ijk(d, qs[m], i, j, k);
         const Axis ax = axis_of(i, d.nx, d.px), ay = axis_of(j, d.ny, d.py), az = axis_of(k, d.nz, d.pz);
         const int sy = d.mx, sz = d.mx * d.my, cy = d.nx, cz = d.nx * d.ny;
-        // neighbour offsets, 16 bits each
-        auto pack = [](int lo, int hi) { return (lo & 0xffff) | (int)((unsigned)hi << 16); };
-        off[m][0] = pack(ax.nd[0] - i, ax.nd[2] - i);
-        off[m][1] = pack((ay.nd[0] - j) * sy, (ay.nd[2] - j) * sy);
-        off[m][2] = pack((az.nd[0] - k) * sz, (az.nd[2] - k) * sz);
+        // neighbour offsets, 16 bits each (the vector they lead to is only read meanwhile)
+        off[m][0] = pack16(ax.nd[0] - i, ax.nd[2] - i);
+        off[m][1] = pack16((ay.nd[0] - j) * sy, (ay.nd[2] - j) * sy);
+        off[m][2] = pack16((az.nd[0] - k) * sz, (az.nd[2] - k) * sz);
         double ssig = 0.0;
 #pragma unroll
         for (int oz = 0; oz < 2; oz++)
@@ -1204,14 +1203,15 @@ __device__ __forceinline__ long long nd_lds_off(const NdCoarseArgs<T>& a, int l)
 // The four nodes (2 ti + {0, 1}, 2 tj + {0, 1}, k) of place e of a coarse-cycle
 // level, one of each colour, with what does not change between its passes: the
 // 3 x 3 x 2 cell sigmas around them (0 beyond a wall) and the neighbour offsets
-// (16 bits each; a missing neighbour is the node itself and meets sigma 0 only).
+// (16 bits each).  Beside a wall in x or y the node inside stands for the missing
+// one: with sigma 0 its value does not count, but it is of another colour, so no
+// thread writes it in the same pass (the node itself in its place would make the
+// sums read a node of the pass's own colour in the next plane).
 template <typename T>
 struct NdOwn {
     T sg[2][3][3];
     int q0, dz, dy[2], dx[2];
     bool on[4];
-
-    __device__ __forceinline__ static int pack(int lo, int hi) { return (lo & 0xffff) | (int)((unsigned)hi << 16); }
 
     __device__ __forceinline__ void init(const NDims& d, const T* sig, int e)
     {
@@ -1224,11 +1224,11 @@ struct NdOwn {
         const Axis ax = axis_of(i, d.nx, d.px), ay = axis_of(j, d.ny, d.py), az = axis_of(k, d.nz, d.pz);
         const Axis ax1 = axis_of(i + 1, d.nx, d.px), ay1 = axis_of(j + 1, d.ny, d.py);
         q0 = (k * d.my + j) * d.mx + i;
-        dz = pack((az.nd[0] - k) * d.mx * d.my, (az.nd[2] - k) * d.mx * d.my);
-        dy[0] = pack((ay.nd[0] - j) * d.mx, (ay.nd[2] - j) * d.mx);
-        dy[1] = pack((ay1.nd[0] - j - 1) * d.mx, (ay1.nd[2] - j - 1) * d.mx);
-        dx[0] = pack(ax.nd[0] - i, ax.nd[2] - i);
-        dx[1] = pack(ax1.nd[0] - i - 1, ax1.nd[2] - i - 1);
+        dz = pack16((az.nd[0] - k) * d.mx * d.my, (az.nd[2] - k) * d.mx * d.my);
+        dy[0] = steps_beside(ay, j, d.mx);
+        dy[1] = steps_beside(ay1, j + 1, d.mx);
+        dx[0] = steps_beside(ax, i, 1);
+        dx[1] = steps_beside(ax1, i + 1, 1);
 #pragma unroll
         for (int c = 0; c < 4; c++) on[c] = live && i + (c & 1) < d.mx && j + (c >> 1) < d.my;
         // cells i-1, i, i+1 (and so along y) and k-1, k

@@ -47,4 +47,13 @@ constexpr Axis axis_of(int i, int n, int per)
 // nodes of one parity never reads, beside a wall, what it writes.
 constexpr int beside(const Axis& a, int o) { return a.nok[2 * o] ? a.nd[2 * o] : a.nd[2 - 2 * o]; }
 
+// Two offsets of 16 bits in one word (low and high half, signed).
+constexpr int pack16(int lo, int hi) { return (lo & 0xffff) | (int)((unsigned)hi << 16); }
+
+// Offsets from node i to the nodes beside it, `stride` values apart.
+constexpr int steps_beside(const Axis& a, int i, int stride)
+{
+    return pack16((beside(a, 0) - i) * stride, (beside(a, 1) - i) * stride);
+}
+
 }  // namespace mp
