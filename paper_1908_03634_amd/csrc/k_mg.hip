@@ -189,35 +189,6 @@ struct RbPair {
     }
 };
 
-// Pairs along x, rows and planes of a workgroup's box (powers of two), and the
-// threads of the red cells around it along each axis (0 where the box spans
-// the axis: a wrap then stays inside it).
-struct RbBox {
-    int bx, by, bz, lx, ly, lz, hx, hy, hz;  // lx = log2(bx), ...
-    int threads() const { return bx * by * bz + (hx + hy + hz + 63) / 64 * 64; }
-};
-
-constexpr int kRbOwn = 256;    // pairs per box
-constexpr int kRbShared = 1216;  // (bx + 2)(by + 2)(bz + 2) of any box of rb_box
-
-inline RbBox rb_box(const Dims& d)
-{
-    const int np = d.nx / 2;
-    RbBox s;
-    s.bx = pow2_at_least(np, 64);
-    const int rem = kRbOwn / s.bx;
-    s.bz = pow2_at_least(d.nz, rem >= 16 ? 4 : rem >= 4 ? 2 : 1);
-    s.by = pow2_at_least(d.ny, rem / s.bz);
-    s.lx = s.ly = s.lz = 0;
-    while (1 << s.lx < s.bx) s.lx++;
-    while (1 << s.ly < s.by) s.ly++;
-    while (1 << s.lz < s.bz) s.lz++;
-    s.hx = s.bx < np ? 2 * s.by * s.bz : 0;
-    s.hy = s.by < d.ny ? 2 * s.bx * s.bz : 0;
-    s.hz = s.bz < d.nz ? 2 * s.bx * s.by : 0;
-    return s;
-}
-
 template <typename T, int MODE, bool CELL>
 __global__ __launch_bounds__(1024) void k_rb_pair(Dims d, RbBox s, const T* __restrict__ xo, T* __restrict__ xn,
                                                   const T* __restrict__ b, Coef<T> C, T h2, const T* __restrict__ ec)
@@ -335,14 +306,14 @@ __global__ __launch_bounds__(1024) void k_rb_pair(Dims d, RbBox s, const T* __re
 
 bool rb_pair_supported(const Dims& d)
 {
-    return d.nx % 2 == 0 && d.ny % 2 == 0 && d.nz % 2 == 0 && d.n() < (1LL << 31);
+    return rb_extents(d.nx, d.ny, d.nz) && d.n() < (1LL << 31);
 }
 
 template <typename T, int MODE>
 static void rb_pair_launch(const Dims& d, const T* xo, T* xn, const T* b, const Coef<T>& c, T h2, const T* ec,
                            hipStream_t s)
 {
-    const RbBox x = rb_box(d);
+    const RbBox x = rb_box(d.nx, d.ny, d.nz);
     const dim3 grid((d.nx / 2 + x.bx - 1) / x.bx, (d.ny + x.by - 1) / x.by, (d.nz + x.bz - 1) / x.bz);
     if (c.cell)
         hipLaunchKernelGGL((k_rb_pair<T, MODE, true>), grid, dim3(x.threads()), 0, s, d, x, xo, xn, b, c, h2, ec);

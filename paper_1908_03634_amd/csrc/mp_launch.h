@@ -1,15 +1,10 @@
 // mp_launch.h -- launch-shape helpers shared by the kernel files.
 #pragma once
+#include "mp_box.h"
+
 #include <hip/hip_runtime.h>
 
 namespace mp {
-
-inline int pow2_at_least(int n, int cap)
-{
-    int p = 1;
-    while (p < n && p < cap) p <<= 1;
-    return p;
-}
 
 // Block and grid covering an nx x ny x nz box with up to 256 threads per
 // block, x fastest (64 lanes along x when nx allows), no index division.

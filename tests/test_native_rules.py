@@ -21,3 +21,8 @@ def _run(name, tmp_path):
 @pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
 def test_nodes_beside_a_wall_have_the_other_colour(tmp_path):
     _run("nodal_axis", tmp_path)
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="g++ not available")
+def test_pair_sweep_boxes_fit_their_lds_array(tmp_path):
+    _run("pair_box", tmp_path)
