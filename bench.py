@@ -167,7 +167,7 @@ def _roofline(workload, infos, precision):
     avg_s = tot_ms / cnt / 1e3 if cnt else float("nan")
     bytes_per_launch = tot_bytes / cnt if cnt else float("nan")
     achieved = bytes_per_launch / avg_s / 1e9
-    kname = "k_fsw_lds" if infos[-1].get("smooth_form") == 1 else "k_gs_blk"
+    kname = {1: "k_fsw_lds", 2: "k_rb_pair", 3: "k_sweep"}.get(infos[-1].get("smooth_form"), "k_gs_blk")
     kname += "<float>" if precision == "mixed" else "<double>"
     rec = _traffic_record(f"{workload}:{kname}")
     traffic = None

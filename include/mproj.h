@@ -123,6 +123,11 @@ typedef struct mp_config {
     int device;              /* HIP device ordinal */
 } mp_config;
 
+/* Sweeps of the finest level: one launch per colour, or both colours in one
+ * launch by whole rows marching along z, by boxes of cell pairs (levels of
+ * <= 2^18 cells), or by tiles (face coefficients). */
+enum { MP_FORM_PER_COLOUR = 0, MP_FORM_ONE_PASS = 1, MP_FORM_PAIR = 2, MP_FORM_TILED = 3 };
+
 /* Per-call report, filled by mp_mac_project and mp_solve. */
 typedef struct mp_info {
     int outer_iters;         /* residual checks after the first (refinement
@@ -144,9 +149,7 @@ typedef struct mp_info {
     double smooth_ms_total;  /* summed finest-level smoother time (kernel_timing) */
     int smooth_launches;     /* number of launches summed above */
     double smooth_bytes;     /* algorithmic HBM bytes of those launches */
-    int smooth_form;         /* finest-level smoother: 0 = one launch per
-                                colour, 1 = both colours of a sweep in one
-                                launch */
+    int smooth_form;         /* finest-level smoother (MP_FORM_*) */
     int flags;               /* bit 0: stagnation detected */
 } mp_info;
 

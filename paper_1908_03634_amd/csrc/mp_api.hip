@@ -1213,6 +1213,16 @@ void record_setup_time(mp_ctx* c)
     if (hipEventElapsedTime(&ms, c->evm[0], c->evm[1]) == hipSuccess) c->ms_setup = ms;
 }
 
+// The form of the finest level's sweeps (the choice that smooth() makes).
+int smooth_form(const mp_ctx* c)
+{
+    const Level& L = c->lv[0];
+    if (L.pair) return MP_FORM_PAIR;
+    if (L.fsw && (use_blk(c, 0) || use_blkf(c, 0))) return MP_FORM_ONE_PASS;
+    if (L.fused && !c->cell_mode) return MP_FORM_TILED;
+    return MP_FORM_PER_COLOUR;
+}
+
 void finish_timing(mp_ctx* c, mp_info* info)
 {
     if (!info) return;
@@ -1235,7 +1245,7 @@ void finish_timing(mp_ctx* c, mp_info* info)
         info->smooth_launches = cnt;
         info->smooth_bytes = bytes;
     }
-    info->smooth_form = c->lv[0].fsw ? 1 : 0;
+    info->smooth_form = smooth_form(c);
 }
 
 void reset_info(mp_info* info)

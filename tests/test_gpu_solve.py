@@ -435,3 +435,27 @@ def test_rhs_checks_on_the_blocked_path(case):
     assert info2["rhs_mean"] == pytest.approx(ref["mean"], rel=1e-9, abs=1e-14)
     ctx.close()
     ctx2.close()
+
+
+# the report names the form that the finest level's sweeps took: boxes of pairs on
+# small levels (2), whole rows on larger ones (1), tiles on stored faces (3), one
+# launch per colour when asked for (0)
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("shape,faces,kw,form", [((32, 32, 32), False, {}, 2), ((32, 32, 32), True, {}, 2),
+                                                 ((128, 64, 64), False, {}, 1), ((128, 64, 64), True, {}, 1),
+                                                 ((32, 32, 32), False, dict(smoother="per_colour"), 0),
+                                                 ((128, 64, 64), False, dict(smoother="per_colour"), 0),
+                                                 ((64, 16, 16), True, dict(smoother="fused", blocked=False), 3),
+                                                 ((9, 9, 9), True, {}, 0)])
+def test_report_names_the_smoother(shape, faces, kw, form, precision):
+    nx, ny, nz = shape
+    say("smooth_form", shape, faces, kw, precision)
+    p = W.planar_problem(nx=nx, ny=ny, nz=nz, contrast=1e2, bc=(1, 1, 1), seed=350)
+    ctx = mproj.Context(nx, ny, nz, h=p.h, bc=p.bc, precision=precision, **kw)
+    if faces:
+        ctx.set_coefs(*(T(c) for c in W.random_coefs(nx, ny, nz, p.bc, 351)))
+    else:
+        ctx.map_base_state(p.geometry, T(p.beta0_1d), T(p.rho), p.dr, p.center, want_coefs=False)
+    _, info = ctx.solve(T(W.random_cells(nx, ny, nz, 352)))
+    assert info["smooth_form"] == form
+    ctx.close()
