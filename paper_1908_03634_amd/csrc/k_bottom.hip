@@ -15,6 +15,13 @@
 // barriers an iteration.  Per solve of 25 x 15 x 11 cells (FP32 coefficients,
 // about 170 iterations) 1.35 ms, 5.05 ms with every vector in global memory;
 // 9 x 9 x 11 cells 0.18 ms, 0.95 ms.
+//
+// A solve that ends without the tolerance returns the iterate of the smallest
+// residual.  Each step copies that iterate to global memory as it leaves it, a
+// store that nothing waits for: 2% of an iteration where vectors are in global
+// memory and 6% where FP64 coefficients already spill (3073 to 5120 cells).
+// (25^3 cells capped at 40 iterations, nine solves: 22.8 ms; 44.3 ms when the
+// solve was run again up to that iterate, 46.7 ms by the form before that.)
 #include "mp_device.h"
 #include "mp_kernels.h"
 #include "mp_krylov.h"
@@ -84,7 +91,6 @@ __global__ __launch_bounds__(1024 / VJ) void k_bottom(Dims d, const T* __restric
                                                  const double* __restrict__ skip_if_direct)
 {
     constexpr int N = M > 0 ? M : 1;
-    // (twenty cells' FP64 coefficients do not fit: read again, from L2)
     constexpr int TH = 1024 / VJ;
     constexpr bool HOLD = M > 0 && VJ > 1;
     using HT = std::conditional_t<(M > 6), T, double>;  // (six cells' FP64 coefficients fit, ten cells' do not)
@@ -99,6 +105,7 @@ __global__ __launch_bounds__(1024 / VJ) void k_bottom(Dims d, const T* __restric
     const int n = (int)d.n();
     const int tid = (int)threadIdx.x, nt = TH;
     double* lab = work;
+    double* const xb = work + 9 * (long long)n;  // the iterate of the smallest residual
     double* const vb = M > 0 ? bufB : bufA;
     const double inv_h2 = 1.0 / h2;
     int half = 0;
@@ -281,110 +288,106 @@ __global__ __launch_bounds__(1024 / VJ) void k_bottom(Dims d, const T* __restric
         return (cs * y[q] - s) * inv_h2;
     };
 
-    // Iterations up to `most`; when the tolerance is not reached the solve is
-    // run again up to the iteration of the smallest residual (the same
-    // operations, so that iterate comes back without having been kept).
-    int most = maxit, counted = 0;
+    part_means([&](int u) { return (double)bin[cell(u)]; });
+    each([&](int u, int) {
+        const double x0 = use_x0 && live(u) ? (double)xout[cell(u)] : 0.0;
+        X(u) = x0;
+        if constexpr (M > 0) P(u) = x0;
+        publish(u, x0);
+    });
+    if (use_x0) __syncthreads();
+    double p0[1][VJ] = {};
+    each([&](int u, int g) {
+        const double rq = live(u) ? ((double)bin[cell(u)] - TV(u)) - (use_x0 ? apply(u, bufA) : 0.0) : 0.0;
+        R(u) = rq;
+        H(u) = rq;
+        V(u) = 0.0;
+        p0[0][g] = fma(rq, rq, p0[0][g]);
+    });
+    totals<VJ, 1>(p0, s1, red, half);  // (all reads of the published x are done)
+    each([&](int u, int) { P(u) = 0.0; });
+    const double bnorm2 = s1[0], tol2 = rtol * rtol * bnorm2;
+    double rho = 1.0, alpha = 1.0, omega = 1.0;
+    // squared residual of the current iterate and of the best one, which is the
+    // current one (`best`) or lies in xb: a step copies it there as it leaves it
+    double rr_cur = bnorm2, rr_best = bnorm2, rho1 = bnorm2;
+    bool best = true;
+    int it = 0;  // iterations begun (each ends in a break or a full step)
+    if (bnorm2 > 0.0) {
 #pragma unroll 1
-    for (int run = 0; run < 2; run++) {
-        part_means([&](int u) { return (double)bin[cell(u)]; });
-        each([&](int u, int) {
-            const double x0 = use_x0 && live(u) ? (double)xout[cell(u)] : 0.0;
-            X(u) = x0;
-            if constexpr (M > 0) P(u) = x0;
-            publish(u, x0);
-        });
-        if (use_x0) __syncthreads();
-        double p0[1][VJ] = {};
-        each([&](int u, int g) {
-            const double rq =
-                live(u) ? ((double)bin[cell(u)] - TV(u)) - (use_x0 ? apply(u, bufA) : 0.0) : 0.0;
-            R(u) = rq;
-            H(u) = rq;
-            V(u) = 0.0;
-            p0[0][g] = fma(rq, rq, p0[0][g]);
-        });
-        totals<VJ, 1>(p0, s1, red, half);  // (all reads of the published x are done)
-        each([&](int u, int) { P(u) = 0.0; });
-        const double bnorm2 = s1[0], tol2 = rtol * rtol * bnorm2;
-        double rho = 1.0, alpha = 1.0, omega = 1.0;
-        // squared residual of the current iterate and of the best full step
-        double rr_cur = bnorm2, rr_best = bnorm2, rho1 = bnorm2;
-        int best = 0, it = 0;  // `it`: iterations begun (each ends in a break or a full step)
-        if (bnorm2 > 0.0) {
-#pragma unroll 1
-            for (; it < most; it++) {
-                if (rho1 == 0.0) break;
-                const double beta = (rho1 / rho) * (alpha / omega);
-                each([&](int u, int) {
-                    const double p = R(u) + beta * (P(u) - omega * V(u));
-                    P(u) = p;
-                    publish(u, p);
-                });
-                __syncthreads();
-                double a1[1][VJ] = {};
-                each([&](int u, int g) {
-                    const double v = apply(u, bufA);
-                    V(u) = v;
-                    a1[0][g] = fma(H(u), v, a1[0][g]);
-                });
-                totals<VJ, 1>(a1, s1, red, half);
-                if (s1[0] == 0.0) break;
-                alpha = rho1 / s1[0];
-                double a2[1][VJ] = {};
-                each([&](int u, int g) {
-                    const double s = R(u) - alpha * V(u);
-                    R(u) = s;
-                    publish(u, s);
-                    a2[0][g] = fma(s, s, a2[0][g]);
-                });
-                totals<VJ, 1>(a2, s1, red, half);
-                const double ss = s1[0];
-                if (ss <= tol2) {
-                    each([&](int u, int) { X(u) += alpha * P(u); });
-                    rr_cur = ss;
-                    break;
-                }
-                double a3[2][VJ] = {};
-                each([&](int u, int g) {
-                    const double t = apply(u, vb);
-                    TV(u) = t;
-                    a3[0][g] = fma(t, R(u), a3[0][g]);
-                    a3[1][g] = fma(t, t, a3[1][g]);
-                });
-                totals<VJ, 2>(a3, s2, red, half);
-                if (s2[1] == 0.0) {
-                    rr_cur = ss;
-                    break;
-                }
-                omega = s2[0] / s2[1];
-                // the residual's norm and the next iteration's rho1 share an exchange
-                double a4[2][VJ] = {};
-                each([&](int u, int g) {
-                    const double s = R(u);
-                    X(u) += alpha * P(u) + omega * s;
-                    const double r = s - omega * TV(u);
-                    R(u) = r;
-                    a4[0][g] = fma(r, r, a4[0][g]);
-                    a4[1][g] = fma(H(u), r, a4[1][g]);
-                });
-                totals<VJ, 2>(a4, s2, red, half);
-                rho = rho1;
-                rr_cur = s2[0];
-                rho1 = s2[1];
-                if (rr_cur <= tol2 || omega == 0.0) break;
-                if (rr_cur < rr_best) {
-                    rr_best = rr_cur;
-                    best = it + 1;
-                }
+        for (; it < maxit; it++) {
+            if (rho1 == 0.0) break;
+            const double beta = (rho1 / rho) * (alpha / omega);
+            each([&](int u, int) {
+                const double p = R(u) + beta * (P(u) - omega * V(u));
+                P(u) = p;
+                publish(u, p);
+            });
+            __syncthreads();
+            double a1[1][VJ] = {};
+            each([&](int u, int g) {
+                const double v = apply(u, bufA);
+                V(u) = v;
+                a1[0][g] = fma(H(u), v, a1[0][g]);
+            });
+            totals<VJ, 1>(a1, s1, red, half);
+            if (s1[0] == 0.0) break;
+            alpha = rho1 / s1[0];
+            double a2[1][VJ] = {};
+            each([&](int u, int g) {
+                const double s = R(u) - alpha * V(u);
+                R(u) = s;
+                publish(u, s);
+                a2[0][g] = fma(s, s, a2[0][g]);
+            });
+            totals<VJ, 1>(a2, s1, red, half);
+            const double ss = s1[0];
+            if (ss <= tol2) {
+                each([&](int u, int) { X(u) += alpha * P(u); });
+                rr_cur = ss;
+                break;
             }
+            double a3[2][VJ] = {};
+            each([&](int u, int g) {
+                const double t = apply(u, vb);
+                TV(u) = t;
+                a3[0][g] = fma(t, R(u), a3[0][g]);
+                a3[1][g] = fma(t, t, a3[1][g]);
+            });
+            totals<VJ, 2>(a3, s2, red, half);
+            if (s2[1] == 0.0) {
+                rr_cur = ss;
+                break;
+            }
+            omega = s2[0] / s2[1];
+            // the residual's norm and the next iteration's rho1 share an exchange
+            double a4[2][VJ] = {};
+            each([&](int u, int g) {
+                const double s = R(u), x = X(u);
+                if (best && live(u)) xb[cell(u)] = x;
+                X(u) = x + (alpha * P(u) + omega * s);
+                const double r = s - omega * TV(u);
+                R(u) = r;
+                a4[0][g] = fma(r, r, a4[0][g]);
+                a4[1][g] = fma(H(u), r, a4[1][g]);
+            });
+            totals<VJ, 2>(a4, s2, red, half);
+            rho = rho1;
+            rr_cur = s2[0];
+            rho1 = s2[1];
+            const bool better = rr_cur < rr_best;
+            best = false;
+            if (rr_cur <= tol2 || omega == 0.0) break;
+            if (better) rr_best = rr_cur;
+            best = better;
         }
-        if (run == 0) counted = it < maxit ? it + (bnorm2 > 0.0 ? 1 : 0) : it;
-        if (run == 1 || rr_cur <= tol2) break;
-        most = best;
-        __syncthreads();
     }
-    if (iters && tid == 0) iters[0] += (double)counted;
+    // the iterate when converged, else the best one (a thread reads what it wrote)
+    if (!(rr_cur <= tol2) && !best)
+        each([&](int u, int) {
+            if (live(u)) X(u) = xb[cell(u)];
+        });
+    if (iters && tid == 0) iters[0] += (double)(it < maxit ? it + (bnorm2 > 0.0 ? 1 : 0) : it);
     part_means([&](int u) { return X(u); });
     each([&](int u, int) {
         if (live(u)) xout[cell(u)] = (T)(X(u) - TV(u));

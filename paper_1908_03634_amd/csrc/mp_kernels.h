@@ -137,7 +137,7 @@ void launch_prolong(const Dims& fine, T* phi, const T* coarse_phi, hipStream_t s
 // workgroup), made mean-zero on each connected part of the grid; stops at
 // ||r|| <= rtol ||r0|| or after maxit iterations, with the iterate of the
 // smallest residual; work = kBottomWork * n doubles.
-constexpr int kBottomWork = 9;
+constexpr int kBottomWork = 10;
 // use_x0: start from phi (tolerance relative to the initial residual).
 // iters: device counter the iterations are added to, or nullptr.
 // skip_if_direct: a device flag (1: the direct bottom solve applies and this

@@ -235,6 +235,62 @@ def test_krylov_bottom_on_a_split_grid(n):
     ctx.close()
 
 
+def _bicgstab(A, b, steps):
+    """Squared residuals and iterates of `steps` BiCGStab steps from zero."""
+    x, r, p, v = np.zeros_like(b), b.copy(), np.zeros_like(b), np.zeros_like(b)
+    rho = alpha = omega = 1.0
+    rr, xs = [r @ r], [x]
+    for _ in range(steps):
+        rho1 = b @ r
+        p = r + (rho1 / rho) * (alpha / omega) * (p - omega * v)
+        v = A @ p
+        alpha = rho1 / (b @ v)
+        s = r - alpha * v
+        t = A @ s
+        omega = (t @ s) / (t @ t)
+        x = x + alpha * p + omega * s
+        r = s - omega * t
+        rho = rho1
+        rr.append(r @ r)
+        xs.append(x)
+    return np.array(rr), xs
+
+
+# one-level grids for each form of the bottom kernel (up to 256, 512, 1024, 3072 and
+# 5120 cells, and beyond); coefficients over six decades make the residual rise on
+# the way, so that an iteration cap ends on a step that is not the best one
+@pytest.mark.parametrize("shape,seed", [((5, 7, 7), 1), ((7, 7, 9), 1), ((9, 9, 9), 2), ((13, 13, 13), 1),
+                                        ((15, 15, 17), 2), ((17, 17, 19), 1), ((17, 17, 19), 2)])
+def test_capped_bottom_returns_the_best_iterate(shape, seed):
+    nx, ny, nz = shape
+    say("capped bottom", shape, seed)
+    bc, h, caps = (1, 1, 1), 1.0 / nz, 13
+    rng = np.random.default_rng(seed)
+    cs = [c * 10.0 ** (6.0 * (rng.random(c.shape) - 0.5)) for c in W.random_coefs(nx, ny, nz, bc, 361)]
+    rhs = np.zeros((nz, ny, nx))
+    rhs[1, 1, 1], rhs[-2, -2, -2] = 1.0, -1.0
+    A = -pins.operator(nx, ny, nz, h, bc, *cs)
+    b = -rhs.ravel()
+    rr, xs = _bicgstab(A, b, caps)
+    best = [int(np.argmin(rr[: cap + 1])) for cap in range(caps + 1)]
+    assert any(0 < best[cap] < cap for cap in range(1, caps + 1))
+    # the same steps with the cells in another order: what rounding alone changes
+    q = np.random.default_rng(99).permutation(len(b))
+    _, ys = _bicgstab(A[q][:, q], b[q], caps)
+    for cap in range(1, caps + 1):
+        kept = xs[best[cap]]
+        other = np.empty_like(kept)
+        other[q] = ys[best[cap]]
+        tol = 1e3 * max(np.abs(other - kept).max(), 1e-15 * np.abs(kept).max())
+        ctx = mproj.Context(nx, ny, nz, h=h, bc=bc, precision="fp64", rtol=1e-14, bottom_rtol=1e-14,
+                            bottom_max_iter=cap, max_outer=1, cycles_per_outer=1)
+        ctx.set_coefs(*(T(c) for c in cs))
+        x, info = ctx.solve(T(rhs), allow_not_converged=True)
+        assert info["vcycles"] == 1 and info["bottom_iters_total"] == cap
+        assert np.abs(N(x).ravel() - (kept - kept.mean())).max() <= tol, (cap, best[cap])
+        ctx.close()
+
+
 @pytest.mark.parametrize("precision,coarse_cycle", [("fp64", True), ("fp64", False), ("mixed", True), ("mixed", False)])
 @pytest.mark.parametrize("n", [16, 32])
 def test_disconnected_bottom_falls_back_to_conjugate_gradients(precision, coarse_cycle, n):
