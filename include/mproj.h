@@ -96,13 +96,14 @@ typedef struct mp_config {
                                 HIP events (mp_info.smooth_*) */
     int smoother;            /* MP_SMOOTH_AUTO: both colours of a sweep in one
                                 launch wherever it pays: register-blocked
-                                levels whose rows of up to 512 cells (FP64:
-                                256) split into equal strips of 2, 4, 6 or 8
-                                cells over a wavefront, face-coefficient levels of >= 4M cells
-                                (tiled), and levels of <= 2^18 cells with even
-                                extents (one
-                                red and one black cell per thread); one launch
-                                per colour elsewhere.
+                                levels of more than 2^18 cells whose rows of
+                                up to 512 cells (FP64: 256) split into equal
+                                strips of 2, 4, 6 or 8 cells over a wavefront
+                                (not periodic rows that leave one lane of it),
+                                face-coefficient levels of >= 4M cells (tiled),
+                                and levels of <= 2^18 cells with even extents
+                                (one red and one black cell per thread); one
+                                launch per colour elsewhere.
                                 MP_SMOOTH_PER_COLOUR: one launch per colour on
                                 every level; MP_SMOOTH_FUSED: both colours in
                                 one launch wherever the grid allows.  All
@@ -117,8 +118,10 @@ typedef struct mp_config {
                                 mp_map_base_state), nx % 128 == 0 (or nx
                                 even, >= 64 and more than 2^18 cells),
                                 ny % 4 == 0, nz is even and >= 4, and the
-                                solution array is 16-byte aligned; 0: one
-                                cell per thread.  Same bits in FP64. */
+                                solution array is 16-byte aligned (FP64 rows
+                                of <= 256 cells: only where the one-pass sweep
+                                fills the device); 0: one cell per thread.
+                                Same bits in FP64. */
     void *stream;            /* hipStream_t for every launch; NULL = null stream */
     int device;              /* HIP device ordinal */
 } mp_config;

@@ -491,6 +491,14 @@ struct FswShape {
 };
 constexpr int kFswMinPlanes = 8;
 
+long long fsw64_workgroups(const Dims& d)
+{
+    const int R = fsw_pairs(d) == 1 ? FswShape<double, 1, FS_PLAIN, false, true>::R
+                                    : FswShape<double, 2, FS_PLAIN, false, true>::R;
+    const int chunks = d.nz / kFswMinPlanes;
+    return (long long)((d.ny + R - 1) / R) * (chunks > 1 ? chunks : 1);
+}
+
 // Planes per chunk.  Each workgroup marches lz + 2 plane steps, and the
 // per-plane critical path (barrier, LDS round trips, the two updates) rather
 // than HBM bounds a workgroup, so the sweep takes about (rounds of resident

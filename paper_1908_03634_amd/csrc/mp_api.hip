@@ -1375,7 +1375,6 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
             return mp::blk_supported(e) &&
                    (e.nx % 128 == 0 || e.n() > kPairMaxCells || cfg->smoother == MP_SMOOTH_FUSED);
         };
-        c->lv[0].blk = cfg->blocked && nlev >= 2 && blocked_pays(c->d0);
         // both colours of a sweep in one pass through LDS (half the bytes of two
         // colour passes; bitwise the same), unless colour passes are asked for;
         // small levels take the pair sweep below (128 x 64 x 32: FP64 1.3x,
@@ -1385,7 +1384,20 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
                    (cfg->smoother == MP_SMOOTH_FUSED ||
                     (cfg->smoother == MP_SMOOTH_AUTO && e.n() > kPairMaxCells));
         };
-        c->lv[0].fsw = c->lv[0].blk && one_pass(c->d0);
+        // FP64 cell values: the sweep forms five true divisions a cell, which
+        // half-filled wavefronts and idle CUs cost more than its bytes save.
+        // Projections against the one-cell kernels: 64-cell rows 1.13 to 1.33 of
+        // their time (64 x 64 x 80 to 64 x 256 x 256), fewer workgroups than CUs
+        // 1.04 to 1.14 (128 x 96 x 96 1.06, 256 x 64 x 80 1.07); at 256
+        // workgroups 0.87 to 1.02 (128^3 0.87, 72 x 128 x 128 0.99, 160 x 64 x
+        // 128 1.01), 256^3 0.65.  FP64 on stored faces 0.66 to 0.98 and FP32 0.54
+        // to 1.00 over the same grids; FP64 colour passes on rows of 257 cells
+        // and more 0.81 to 1.02.
+        auto cells64_pay = [&](const Dims& e) {
+            return !one_pass(e) || cfg->smoother == MP_SMOOTH_FUSED ||
+                   (e.nx > 64 && mp::fsw64_workgroups(e) >= 256);
+        };
+        c->lv[0].blk = cfg->blocked && nlev >= 2 && blocked_pays(c->d0) && (mx || cells64_pay(c->d0));
         for (int l = 0; l < nlev - 1; l++) {
             Level& L = c->lv[l];
             if (c->coarse_start >= 0 && l >= c->coarse_start) break;
@@ -1393,7 +1405,7 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
             // many registers)
             L.blkf = cfg->blocked && blocked_pays(L.d) && (mx || one_pass(L.d));
             // both colours of a sweep in one pass
-            if (l > 0) L.fsw = L.blkf && one_pass(L.d);
+            L.fsw = (L.blkf || L.blk) && one_pass(L.d);
             L.fused = !L.blkf && mp::sweep_supported(L.d) &&
                       (cfg->smoother == MP_SMOOTH_FUSED ||
                        (cfg->smoother == MP_SMOOTH_AUTO && L.d.n() >= kFusedMinCells));

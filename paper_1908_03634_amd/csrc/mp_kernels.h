@@ -250,6 +250,8 @@ void launch_rb_pair(const Dims& d, const T* xo, T* xn, const T* b, const Coef<T>
                     hipStream_t s);
 bool fsw_supported(const Dims& d);
 bool fsw64_supported(const Dims& d);  // ... in FP64
+// Workgroups that an FP64 sweep can be cut into (fsw64_supported(d)).
+long long fsw64_workgroups(const Dims& d);
 template <typename T>
 void launch_fsw_blk(const Dims& d, const T* xo, T* xn, const T* b, const T* cc, T h2, int mode, const T* ec,
                     double* phi, const double* irs, int irf, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s);

@@ -294,3 +294,29 @@ def test_pair_sweep_equals_colour_passes(shape, bc, precision):
         ctx.close()
     assert np.array_equal(out[0][0], out[1][0])
     assert np.array_equal(out[0][1], out[1][1])
+
+
+# where the FP64 one-pass sweep on cell values begins: rows past half a wavefront
+# and a workgroup for each of 256 CUs; stored faces take it at every size above
+@pytest.mark.parametrize("faces", [False, True])
+@pytest.mark.parametrize("shape,form", [((96, 128, 128), 1), ((128, 96, 96), 0), ((64, 128, 136), 0),
+                                        ((160, 128, 64), 1), ((256, 64, 64), 0)])
+def test_fp64_sweep_forms_by_size(shape, form, faces):
+    say("fp64 forms", shape, faces)
+    nx, ny, nz = shape
+    bc = (1, 0, 1)
+    p = _problem(shape, bc, 6400 + sum(shape))
+    rhs = W.random_cells(*shape, 6450 + sum(shape))
+    cs = [T(c) for c in W.random_coefs(nx, ny, nz, bc, 6460)] if faces else None
+    out = []
+    for kw in ({}, dict(smoother="per_colour"), dict(blocked=False)):
+        ctx = context_for(p, "fp64", max_outer=2, nu1=1, nu2=2, **kw)
+        if faces:
+            ctx.set_coefs(*cs)
+        else:
+            ctx.map_base_state(p.geometry, T(p.beta0_1d), T(p.rho), p.dr, p.center, want_coefs=False)
+        x, info = ctx.solve(T(rhs), allow_not_converged=True)
+        out.append((N(x), info["smooth_form"]))
+        ctx.close()
+    assert [f for _, f in out] == [1 if faces else form, 0, 0]
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][0], out[2][0])

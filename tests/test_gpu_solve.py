@@ -498,7 +498,7 @@ def test_rhs_checks_on_the_blocked_path(case):
 # launch per colour when asked for (0)
 @pytest.mark.parametrize("precision", ["fp64", "mixed"])
 @pytest.mark.parametrize("shape,faces,kw,form", [((32, 32, 32), False, {}, 2), ((32, 32, 32), True, {}, 2),
-                                                 ((128, 64, 64), False, {}, 1), ((128, 64, 64), True, {}, 1),
+                                                 ((128, 128, 128), False, {}, 1), ((128, 64, 64), True, {}, 1),
                                                  ((32, 32, 32), False, dict(smoother="per_colour"), 0),
                                                  ((128, 64, 64), False, dict(smoother="per_colour"), 0),
                                                  ((64, 16, 16), True, dict(smoother="fused", blocked=False), 3),
