@@ -927,37 +927,44 @@ int nd_setup(mp_ctx* c)
         L.h = h;
         L.nn = (long long)L.d.mx * L.d.my * L.d.mz;
         L.col = c->cfg.blocked && mp::nd_col_supported(L.d);
-        if (L.col && c->cfg.smoother != MP_SMOOTH_PER_COLOUR) {
-            // whole rows per wavefront where they stream (128 x 128 x 129: 8.7 us
-            // a pass), the parallel form where latency counts (64 x 64 x 65: 5.6
-            // us, 6.9 by rows; 32 x 32 x 33: 4.6, 6.2)
-            L.pair_any = !(mx && mp::nd_pair_supported(L.d) &&
-                           (c->cfg.smoother == MP_SMOOTH_FUSED || L.nn > (1 << 19)));
-            L.pair = !L.pair_any || mp::nd_pair_any_supported(L.d);
-        }
         N->lv.push_back(L);
         if (!can_coarsen(d.nx, d.ny, d.nz)) break;
         d = Dims{d.nx / 2, d.ny / 2, d.nz / 2, d.px, d.py, d.pz};
         h *= 2.0;
     }
-    {
+    auto allocate = [&](int smoother) {
         const int np1 = mp::red_blocks(N->lv[0].nn), np2 = mp::nd_col_reduce_blocks(N->lv[0].d);
         N->mem.add(&N->partials, sizeof(double) * (np1 > np2 ? np1 : np2));
-    }
-    d = c->d0;
-    for (int l = 0; l < (int)N->lv.size(); l++) {
-        NLevel& L = N->lv[l];
-        if (mx || l > 0) {
-            N->mem.add(&L.x, tsz * L.nn);
-            N->mem.add(&L.b, tsz * L.nn);
-            N->mem.add(&L.sig, tsz * d.n());
+        Dims e = c->d0;
+        bool second = false;
+        for (int l = 0; l < (int)N->lv.size(); l++) {
+            NLevel& L = N->lv[l];
+            L.pair = L.pair_any = false;
+            if (L.col && smoother != MP_SMOOTH_PER_COLOUR) {
+                // whole rows per wavefront where they stream (128 x 128 x 129: 8.7 us
+                // a pass), the parallel form where latency counts (64 x 64 x 65: 5.6
+                // us, 6.9 by rows; 32 x 32 x 33: 4.6, 6.2)
+                L.pair_any = !(mx && mp::nd_pair_supported(L.d) &&
+                               (smoother == MP_SMOOTH_FUSED || L.nn > (1 << 19)));
+                L.pair = !L.pair_any || mp::nd_pair_any_supported(L.d);
+            }
+            if (mx || l > 0) {
+                N->mem.add(&L.x, tsz * L.nn);
+                N->mem.add(&L.b, tsz * L.nn);
+                N->mem.add(&L.sig, tsz * e.n());
+            }
+            N->mem.add(&L.r, tsz * L.nn);
+            L.x2 = nullptr;
+            if (L.pair) {
+                N->mem.add(&L.x2, tsz * L.nn);
+                second = true;
+            }
+            e = Dims{e.nx / 2, e.ny / 2, e.nz / 2, e.px, e.py, e.pz};
         }
-        N->mem.add(&L.r, tsz * L.nn);
-        if (L.pair) N->mem.add(&L.x2, tsz * L.nn);
-        d = Dims{d.nx / 2, d.ny / 2, d.nz / 2, d.px, d.py, d.pz};
-    }
-    N->mem.add(&N->b64, sizeof(double) * N->lv[0].nn);
-    N->mem.add(&N->bottom_work, sizeof(double) * 4 * N->lv.back().nn);
+        N->mem.add(&N->b64, sizeof(double) * N->lv[0].nn);
+        N->mem.add(&N->bottom_work, sizeof(double) * 4 * N->lv.back().nn);
+        return N->mem.commit() && !(second && test_fail_alloc("second_buffers"));
+    };
     // single-workgroup coarse cycle: the trailing levels whose arrays fit LDS
     if (c->cfg.coarse_cycle) {
         const int nlev = (int)N->lv.size();
@@ -974,8 +981,16 @@ int nd_setup(mp_ctx* c)
         N->coarse_start = (nlev >= 3 && fits(lc) && lc < nlev - 1) ? lc : -1;
     }
     N->nb = mp::red_blocks(N->lv[0].nn);
-    if (!N->mem.commit()) {
+    // (in place where only that fits, as in mp_init)
+    bool good = allocate(c->cfg.smoother);
+    if (!good && c->cfg.smoother == MP_SMOOTH_AUTO) {
         (void)hipGetLastError();
+        N->mem.release();
+        good = allocate(MP_SMOOTH_PER_COLOUR);
+    }
+    if (!good) {
+        (void)hipGetLastError();
+        N->mem.release();
         delete N;
         c->nd = nullptr;
         return fail(c, MP_ERR_NOMEM, "no device memory for the nodal hierarchy");
@@ -1319,9 +1334,6 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
     const bool mx = mixed(c);
     const size_t tsz = mx ? sizeof(float) : sizeof(double);
     bool good = true;
-    auto doubles = [&](double** dst, long long n) { c->mem.add(dst, sizeof(double) * (size_t)n); };
-    for (double** q : {&c->c64x, &c->c64y, &c->c64z, &c->beta0, &c->ccell, &c->b64}) doubles(q, c->n0);
-    if (mx) c->mem.add(&c->ccell32, sizeof(float) * (size_t)c->n0);
     c->nbz = mp::zred_blocks(c->d0);
     {
         int np = c->nbz > mp::kMaxRedBlocks ? c->nbz : mp::kMaxRedBlocks;
@@ -1331,10 +1343,8 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
             np = 2 * mp::proj_blk_reduce_blocks(c->d0);
         // and so does the one-cell right-hand side (b, b^2 per z-column block)
         if (2 * c->nbz > np) np = 2 * c->nbz;
-        doubles(&c->partials, np);
         c->npartials = np;
     }
-    doubles(&c->dscal, kScal);
     // levels
     Dims d = c->d0;
     double h = cfg->h;
@@ -1347,13 +1357,11 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
         d = Dims{d.nx / 2, d.ny / 2, d.nz / 2, d.px, d.py, d.pz};
         h *= 2.0;
     }
-    doubles(&c->bottom_work, mp::kBottomWork * c->lv.back().d.n());
-    if (c->lv.back().d.n() <= mp::kDirectBottomCells)
-        doubles(&c->ginv, mp::kDirectBottomCells * mp::kDirectBottomCells);
-    // single-workgroup coarse cycle: trailing levels of <= kCoarseCells cells,
-    // when the bottom fits one wavefront and there is more than one level
-    {
+    // kernels of each level, by the form of its sweeps (MP_SMOOTH_*)
+    auto choose = [&](int smoother) {
         const int nlev = (int)c->lv.size();
+        // single-workgroup coarse cycle: trailing levels of <= kCoarseCells cells,
+        // when the bottom fits one wavefront and there is more than one level
         c->coarse_start = -1;
         if (cfg->coarse_cycle && nlev >= 2 && c->lv.back().d.n() <= kWaveBottomCells) {
             // bytes of LDS the set of levels from..nlev-1 needs (5 arrays each)
@@ -1373,7 +1381,7 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
         // launch of one or two cells per thread (64^3: 0.95x, 96^3: 1.12x)
         auto blocked_pays = [&](const Dims& e) {
             return mp::blk_supported(e) &&
-                   (e.nx % 128 == 0 || e.n() > kPairMaxCells || cfg->smoother == MP_SMOOTH_FUSED);
+                   (e.nx % 128 == 0 || e.n() > kPairMaxCells || smoother == MP_SMOOTH_FUSED);
         };
         // both colours of a sweep in one pass through LDS (half the bytes of two
         // colour passes; bitwise the same), unless colour passes are asked for;
@@ -1381,8 +1389,8 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
         // mixed 1.2x faster)
         auto one_pass = [&](const Dims& e) {
             return (mx ? mp::fsw_supported(e) : mp::fsw64_supported(e)) &&
-                   (cfg->smoother == MP_SMOOTH_FUSED ||
-                    (cfg->smoother == MP_SMOOTH_AUTO && e.n() > kPairMaxCells));
+                   (smoother == MP_SMOOTH_FUSED ||
+                    (smoother == MP_SMOOTH_AUTO && e.n() > kPairMaxCells));
         };
         // FP64 cell values: the sweep forms five true divisions a cell, which
         // half-filled wavefronts and idle CUs cost more than its bytes save.
@@ -1394,7 +1402,7 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
         // to 1.00 over the same grids; FP64 colour passes on rows of 257 cells
         // and more 0.81 to 1.02.
         auto cells64_pay = [&](const Dims& e) {
-            return !one_pass(e) || cfg->smoother == MP_SMOOTH_FUSED ||
+            return !one_pass(e) || smoother == MP_SMOOTH_FUSED ||
                    (e.nx > 64 && mp::fsw64_workgroups(e) >= 256);
         };
         c->lv[0].blk = cfg->blocked && nlev >= 2 && blocked_pays(c->d0) && (mx || cells64_pay(c->d0));
@@ -1407,25 +1415,51 @@ int mp_init(const mp_config* cfg, mp_ctx** out)
             // both colours of a sweep in one pass
             L.fsw = (L.blkf || L.blk) && one_pass(L.d);
             L.fused = !L.blkf && mp::sweep_supported(L.d) &&
-                      (cfg->smoother == MP_SMOOTH_FUSED ||
-                       (cfg->smoother == MP_SMOOTH_AUTO && L.d.n() >= kFusedMinCells));
+                      (smoother == MP_SMOOTH_FUSED ||
+                       (smoother == MP_SMOOTH_AUTO && L.d.n() >= kFusedMinCells));
             // small levels: both colours in one launch with the red cells around
             // each workgroup's box evaluated again, where a launch costs more
             // than the level's cells.  On larger levels the repeated evaluations
             // cost as much as the second launch: there only when asked for
             // (MP_SMOOTH_FUSED)
             L.pair = !L.fsw && !L.fused && mp::rb_pair_supported(L.d) &&
-                     (cfg->smoother == MP_SMOOTH_FUSED ||
-                      (cfg->smoother == MP_SMOOTH_AUTO && L.d.n() <= kPairMaxCells));
+                     (smoother == MP_SMOOTH_FUSED ||
+                      (smoother == MP_SMOOTH_AUTO && L.d.n() <= kPairMaxCells));
         }
+    };
+    auto allocate = [&]() {
+        auto doubles = [&](double** dst, long long n) { c->mem.add(dst, sizeof(double) * (size_t)n); };
+        for (double** q : {&c->c64x, &c->c64y, &c->c64z, &c->beta0, &c->ccell, &c->b64}) doubles(q, c->n0);
+        if (mx) c->mem.add(&c->ccell32, sizeof(float) * (size_t)c->n0);
+        doubles(&c->partials, c->npartials);
+        doubles(&c->dscal, kScal);
+        doubles(&c->bottom_work, mp::kBottomWork * c->lv.back().d.n());
+        if (c->lv.back().d.n() <= mp::kDirectBottomCells)
+            doubles(&c->ginv, mp::kDirectBottomCells * mp::kDirectBottomCells);
+        bool second = false;
+        for (int l = 0; l < (int)c->lv.size(); l++) {
+            Level& L = c->lv[l];
+            if (mx || l > 0)
+                for (void** q : {&L.x, &L.b, &L.cx, &L.cy, &L.cz}) c->mem.add(q, tsz * L.d.n());
+            L.x2 = nullptr;
+            if (L.fused || L.pair || L.fsw) {
+                c->mem.add(&L.x2, tsz * L.d.n());
+                second = true;
+            }
+        }
+        return c->mem.commit() && !(second && test_fail_alloc("second_buffers"));
+    };
+    // out-of-place sweeps need a second iterate on their levels (1.14 of 7.9 words
+    // a cell in FP64, 0.57 of 9.9 in MIXED): a grid that fits only without them
+    // sweeps in place, one colour per launch (the same bits)
+    choose(cfg->smoother);
+    good = allocate();
+    if (!good && cfg->smoother == MP_SMOOTH_AUTO) {
+        (void)hipGetLastError();
+        c->mem.release();
+        choose(MP_SMOOTH_PER_COLOUR);
+        good = allocate();
     }
-    for (int l = 0; l < (int)c->lv.size(); l++) {
-        Level& L = c->lv[l];
-        if (mx || l > 0)
-            for (void** q : {&L.x, &L.b, &L.cx, &L.cy, &L.cz}) c->mem.add(q, tsz * L.d.n());
-        if (L.fused || L.pair || L.fsw) c->mem.add(&L.x2, tsz * L.d.n());
-    }
-    good = c->mem.commit();
     if (!mx) {
         c->lv[0].b = c->b64;
         c->lv[0].cx = c->c64x;

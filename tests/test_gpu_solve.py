@@ -515,3 +515,32 @@ def test_report_names_the_smoother(shape, faces, kw, form, precision):
     _, info = ctx.solve(T(W.random_cells(nx, ny, nz, 352)))
     assert info["smooth_form"] == form
     ctx.close()
+
+
+# where device memory does not hold the second iterates of the out-of-place sweeps,
+# sweeps run in place, one launch per colour, with the same bits; a smoother asked
+# for by name is refused
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+@pytest.mark.parametrize("shape", [(16, 16, 16), (128, 128, 128), (192, 64, 64)])
+def test_out_of_place_sweeps_without_memory(shape, precision, monkeypatch):
+    nx, ny, nz = shape
+    say("second buffers", shape, precision)
+    p = W.planar_problem(nx=nx, ny=ny, nz=nz, contrast=1e2, bc=(0, 1, 1), seed=370)
+    q = W.planar_problem(nx=nx, ny=ny, nz=nz, contrast=1e2, bc=(0, 1, 1), seed=371, velocity="cells")
+    outs = []
+    for fail in (False, True):
+        if fail:
+            monkeypatch.setenv("MP_TEST_FAIL_ALLOC", "second_buffers")
+            with pytest.raises(mproj.MprojError) as e:
+                context_for(p, precision, smoother="fused")
+            assert e.value.code == 3
+        ctx = context_for(p, precision, rtol=1e-9)
+        ctx.map_base_state(p.geometry, T(p.beta0_1d), T(p.rho), p.dr, p.center, want_coefs=False)
+        ux = T(p.ux)
+        phi, info = ctx.mac_project(ux, T(p.uy), T(p.uz), T(p.S))
+        vx = T(q.ux)
+        pi, _ = ctx.nodal_project(vx, T(q.uy), T(q.uz), T(q.S))
+        assert info["smooth_form"] == 0 or not fail
+        outs.append([N(a) for a in (phi, ux, pi, vx)])
+        ctx.close()
+    assert all(np.array_equal(a, b) for a, b in zip(*outs))
