@@ -308,7 +308,7 @@ __device__ __forceinline__ void ring_shift(Strip<T, M> (&xm)[R], Strip<T, M> (&x
 }
 
 // Coarse right-hand side = mean of the 8 fine residuals of each coarse cell,
-// summed in the order of restrict_cell (z, then y, then x child).  A strip
+// summed by z, then y, then x child (every form of the restriction).  A strip
 // holds the x children of M coarse cells; planes are taken in pairs (chunks
 // start on even planes), rows in pairs (j0 is even).
 template <typename T, int M, int R>

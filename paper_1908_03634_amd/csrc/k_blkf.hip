@@ -205,7 +205,7 @@ __global__ __launch_bounds__(BK_T) void k_gs_blkf(Dims d, int lz, T* __restrict_
     }
 }
 
-// Coarse right-hand side = mean of the 8 fine residuals (restrict_cell order).
+// Coarse right-hand side = mean of the 8 fine residuals (by z, then y, then x child).
 template <typename T, int M, int R>
 __global__ __launch_bounds__(BK_T) void k_rr_blkf(Dims d, int lz, const T* __restrict__ x, const T* __restrict__ b,
                                                   const T* __restrict__ cxa, const T* __restrict__ cya,
@@ -339,18 +339,12 @@ static void gsf_mode(int mode, const Dims& d, T* x, const T* b, const Coef<T>& c
     }
 }
 
-// Strip width: strips of 4 in FP32 rows of whole 256-cell wavefronts, else pairs.
-template <typename T>
-static bool face_pairs(const Dims& d)
-{
-    return sizeof(T) == 8 || d.nx % 256 != 0;
-}
-
+// Strips of 4 in rows of whole 256-cell wavefronts, else pairs.
 template <typename T>
 void launch_gs_blkf(const Dims& d, T* x, const T* b, const Coef<T>& c, T h2, int colour, int mode, const T* ec,
                     hipStream_t s)
 {
-    if (face_pairs<T>(d)) gsf_mode<T, 1>(mode, d, x, b, c, h2, colour, ec, s);
+    if (d.nx % 256 != 0) gsf_mode<T, 1>(mode, d, x, b, c, h2, colour, ec, s);
     else gsf_mode<T, 2>(mode, d, x, b, c, h2, colour, ec, s);
 }
 
@@ -366,8 +360,6 @@ void launch_rr_blkf(const Dims& d, const T* x, const T* b, const Coef<T>& c, T i
 
 template void launch_gs_blkf<float>(const Dims&, float*, const float*, const Coef<float>&, float, int, int,
                                     const float*, hipStream_t);
-template void launch_gs_blkf<double>(const Dims&, double*, const double*, const Coef<double>&, double, int, int,
-                                     const double*, hipStream_t);
 template void launch_rr_blkf<float>(const Dims&, const float*, const float*, const Coef<float>&, float, float*,
                                     hipStream_t);
 template void launch_rr_blkf<double>(const Dims&, const double*, const double*, const Coef<double>&, double, double*,

@@ -651,7 +651,7 @@ __global__ __launch_bounds__(1024) void k_coarse_cycle(CoarseArgs<T> a)
         T* bc = lds_level(a, l + 1, lds).b;
         // residual restriction in two parallel phases: every fine residual
         // into the scratch, then the 8 children of each coarse cell summed in
-        // the order of restrict_cell (the same bits)
+        // the order of the one-launch kernels (the same bits)
         const int nf = (int)f.n();
         const FastDiv fx((unsigned)f.nx), fy((unsigned)f.ny), fxc((unsigned)nxc), fyc((unsigned)nyc);
         const int npair = (f.nx + 1) / 2 * f.ny * f.nz;

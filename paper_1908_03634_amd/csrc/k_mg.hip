@@ -335,7 +335,7 @@ void launch_rb_pair(const Dims& d, const T* xo, T* xn, const T* b, const Coef<T>
 // Coarse right-hand side = mean of the 8 fine residuals, one fine cell per
 // thread (a thread with the eight children of a coarse cell leaves small grids
 // without wavefronts: 32^3 FP64 cell coefficients 12.8 us, 4.1 here), the
-// children then summed through LDS in the order of restrict_cell.  Blocks are
+// children then summed through LDS by z, then y, then x child.  Blocks are
 // boxes of even extents, powers of two.
 template <typename T, bool CELL>
 __global__ __launch_bounds__(256) void k_resid_restrict(Dims d, const T* __restrict__ x, const T* __restrict__ b,

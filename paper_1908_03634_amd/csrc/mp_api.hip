@@ -571,7 +571,9 @@ void smooth(mp_ctx* c, int l, bool zero_init, const T* ec, bool last = false)
             // per colour: x in and out, b, three face words; 1/8 word of e
             const double words = (zi ? 5.0 : 6.0) + (ec ? 0.125 : 0.0);
             timed_begin(c, tm);
-            mp::launch_gs_blkf<T>(L.d, (T*)L.x, (const T*)L.b, C, h2, colour, mode, ec, c->stream);
+            // (FP64 levels of this form sweep in one pass)
+            if constexpr (sizeof(T) == 4)
+                mp::launch_gs_blkf<T>(L.d, (T*)L.x, (const T*)L.b, C, h2, colour, mode, ec, c->stream);
             timed_end(c, tm, words * sizeof(T) * cells);
         }
         return;

@@ -357,20 +357,4 @@ __device__ __forceinline__ T resid_cell(const Dims& d, const T* __restrict__ x, 
                           b[q], inv_h2);
 }
 
-// Coarse right-hand side of coarse cell (I,J,K): mean of the 8 fine residuals.
-template <typename T, bool CELL>
-__device__ __forceinline__ T restrict_cell(const Dims& d, const T* __restrict__ x, const T* __restrict__ b,
-                                           const Coef<T>& C, T inv_h2, int I, int J, int K)
-{
-    T acc = T(0);
-#pragma unroll
-    for (int c = 0; c < 2; c++)
-#pragma unroll
-        for (int bb = 0; bb < 2; bb++)
-#pragma unroll
-            for (int a = 0; a < 2; a++)
-                acc += resid_cell<T, CELL>(d, x, b, C, inv_h2, 2 * I + a, 2 * J + bb, 2 * K + c);
-    return T(0.125) * acc;
-}
-
 }  // namespace mp

@@ -255,12 +255,13 @@ long long fsw64_workgroups(const Dims& d);
 template <typename T>
 void launch_fsw_blk(const Dims& d, const T* xo, T* xn, const T* b, const T* cc, T h2, int mode, const T* ec,
                     double* phi, const double* irs, int irf, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s);
-// The same sweep on a level with stored low-face coefficients c (FP32; equal
-// bit for bit to two launch_gs_blkf colour passes).
+// The same sweep on a level with stored low-face coefficients c (equal bit for
+// bit to two colour passes).
 template <typename T>
 void launch_fsw_blkf(const Dims& d, const T* xo, T* xn, const T* b, const Coef<T>& c, T h2, int mode, const T* ec,
                      hipStream_t s);
-// The same two kernels on a level with stored low-face coefficients c.
+// The same two kernels on a level with stored low-face coefficients c (the colour
+// pass in FP32 only: FP64 levels of this form sweep in one pass).
 template <typename T>
 void launch_gs_blkf(const Dims& d, T* x, const T* b, const Coef<T>& c, T h2, int colour, int mode, const T* ec,
                     hipStream_t s);
