@@ -27,6 +27,8 @@
 #include "mp_device.h"
 #include "mp_kernels.h"
 
+#include <type_traits>
+
 namespace mp {
 
 namespace {
@@ -251,10 +253,11 @@ namespace {
 
 // Where a radius lies among the edges re[0..ne), guessed: edges equally spaced
 // in r (uniform base states) or in r^2 (irregular radii), whichever puts the
-// middle edge nearer to the middle.
+// middle edge nearer to the middle.  `near`: the guess finds the edges at one, four
+// and seven eighths of the table within a few places.
 struct EdgeGuess {
     float a, scale;
-    bool sq;
+    bool sq, near;
 
     template <typename I>
     __device__ __forceinline__ EdgeGuess(const double* __restrict__ re, I ne)
@@ -265,6 +268,15 @@ struct EdgeGuess {
         sq = fabsf(quad - half) < fabsf(lin - half);
         a = sq ? r0 * r0 : r0;
         scale = (float)(ne - 1) / (sq ? rn * rn - a : rn - a);
+        // (a float holds a place to 2^-23 of its value, a square to twice that)
+        const I off = 4 + (ne >> 20);
+        near = true;
+#pragma unroll
+        for (int e = 1; e < 8; e += 3) {
+            const I q = ne / 8 * e, g = at(re[q], ne);
+            near = near && (g > q ? g - q : q - g) <= off;
+        }
+        near = __builtin_amdgcn_readfirstlane(near);  // (the same in every lane)
     }
     // in [0, ne - 2] (0 where it is no number; the float bound may round up)
     template <typename I>
@@ -277,18 +289,22 @@ struct EdgeGuess {
 };
 
 // w0 at radius r, linear between the edges re[0..ne) (sorted), the end
-// values held outside them.  The edge below r is sought from the guess outwards
-// in doubling steps, then by halving: two or three reads of one cache line where
-// the guess holds, against log2(ne) dependent reads across the table.
-template <typename I>
+// values held outside them.  Where guesses are near, the edge below r is sought
+// from the guess outwards in doubling steps, then by halving: two or three reads of
+// one cache line, against log2(ne) dependent reads across the table by halving
+// alone, which other edges take (from a guess far off, steps outwards would
+// double the reads).
+template <bool NEAR, typename I>
 __device__ __forceinline__ double w0_at(const double* __restrict__ w0, const double* __restrict__ re, I ne,
                                         const EdgeGuess& guess, double r)
 {
     if (r >= re[ne - 1]) return w0[ne - 1];
     if (r <= re[0]) return w0[0];
-    I lo = guess.at(r, ne), hi = lo + 1;  // (ne >= 2 here)
+    I lo = NEAR ? guess.at(r, ne) : 0, hi = NEAR ? lo + 1 : ne - 1;  // (ne >= 2 here)
     double rl = re[lo], rh = re[hi];
-    if (rl <= r) {
+    if (!NEAR) {
+        // re[0] < r < re[ne - 1]
+    } else if (rl <= r) {
         for (I step = 2; hi < ne - 1 && rh <= r; step *= 2) {
             lo = hi;
             rl = rh;
@@ -332,7 +348,10 @@ __global__ __launch_bounds__(kBlock) void k_w0_planar(Dims d, const double* __re
 // w0(r_f) (x_f - centre)_axis / r_f.  Each thread takes kW0Faces faces along z.
 // Bound by instructions (a square root and two divisions in FP64 and the edge
 // search; 16 bytes are moved per face).  192^3 cells, irregular radii: 61 us per axis,
-// 151 us with a search by halving and 64-bit coordinates for every face.
+// 151 us with a search by halving and 64-bit coordinates for every face.  The
+// call on 80000 geometric edges 441 us, 20000 cubic ones 353 us, 5000 geometric
+// ones 274 us (halving): 1750, 1113 and 415 us by steps outwards from guesses far
+// off, 464, 369 and 264 us by halving with one face per thread.
 constexpr int kW0Faces = 8;
 
 template <typename I>
@@ -350,15 +369,19 @@ __global__ __launch_bounds__(kBlock) void k_w0_sphere(Dims d, int axis, double h
     const double x = (axis == 0 ? (double)i : i + 0.5) * h - c0;
     const double y = (axis == 1 ? (double)j : j + 0.5) * h - c1;
     const int k1 = min(fz, ((int)blockIdx.y + 1) * kW0Faces);
-    for (int k = (int)blockIdx.y * kW0Faces; k < k1; k++) {
-        if (bz && (k == 0 || k == d.nz)) continue;
-        const double z = (axis == 2 ? (double)k : k + 0.5) * h - c2;
-        const double r = sqrt(x * x + y * y + z * z);
-        if (r > 0.0) {
-            const double comp = axis == 0 ? x : axis == 1 ? y : z;
-            u[k * per + p] += w0_at(w0, re, ne, guess, r) * (comp / r);
+    auto faces = [&](auto near) {
+        for (int k = (int)blockIdx.y * kW0Faces; k < k1; k++) {
+            if (bz && (k == 0 || k == d.nz)) continue;
+            const double z = (axis == 2 ? (double)k : k + 0.5) * h - c2;
+            const double r = sqrt(x * x + y * y + z * z);
+            if (r > 0.0) {
+                const double comp = axis == 0 ? x : axis == 1 ? y : z;
+                u[k * per + p] += w0_at<decltype(near)::value>(w0, re, ne, guess, r) * (comp / r);
+            }
         }
-    }
+    };
+    if (guess.near) faces(std::true_type{});
+    else faces(std::false_type{});
 }
 
 // ------------------------------------------------------------- launchers

@@ -358,3 +358,27 @@ def test_add_w0_on_uneven_edges(edges):
     for a, b in zip(u, ref):
         assert np.abs(N(a) - b).max() <= tol
     ctx.close()
+
+
+# edges that the guess meets at each eighth of the table and misses by hundreds of
+# places between them, on both sides (the search steps outwards from the guess),
+# and the same spacing without that agreement (halving alone)
+@pytest.mark.parametrize("shift", [0.0, 0.04])
+def test_add_w0_on_edges_that_wander_from_the_guess(shift):
+    say("add_w0 wander", shift)
+    p = W.spherical_problem(32, contrast=1e3, seed=7220, base="linear")
+    top = p.h * 32
+    x = np.arange(20001) / 20000.0
+    re = top * (x + 0.015 * (np.sin(16.0 * np.pi * (x + shift)) - np.sin(16.0 * np.pi * shift)))
+    assert (np.diff(re) > 0.0).all()
+    w0 = np.random.default_rng(7221).standard_normal(len(re))
+    ref = oracle.add_w0(oracle.Grid.of(p), 1, w0, re, p.center, p.ux, p.uy, p.uz)
+    ctx = context_for(p, "fp64")
+    ctx.map_base_state(p.geometry, T(p.beta0_1d), T(p.rho), p.dr, p.center, want_coefs=False)
+    u = [T(p.ux), T(p.uy), T(p.uz)]
+    ctx.add_w0(T(w0), *u, re=T(re))
+    slope = np.abs(np.diff(w0) / np.diff(re)).max()
+    tol = 1e-14 * max(np.abs(b).max() for b in ref) + 2.0 * slope * top * 2.0 ** -52
+    for a, b in zip(u, ref):
+        assert np.abs(N(a) - b).max() <= tol
+    ctx.close()
