@@ -12,9 +12,10 @@
 // neighbours; the rest, the coefficients and the neighbour indices in
 // registers), sums are vector-pipeline wavefront sums and one LDS exchange with
 // one barrier each, and sums of the same data share that exchange: five
-// barriers an iteration.  Per solve of 25 x 15 x 11 cells (FP32 coefficients,
-// about 170 iterations) 1.35 ms, 5.05 ms with every vector in global memory;
-// 9 x 9 x 11 cells 0.18 ms, 0.95 ms.
+// barriers an iteration.  An iteration takes 2.6 us at 891 cells, 4.1 us at 3003
+// and 7.1 us at 25 x 15 x 11 (FP32 coefficients; 13.5 us with FP64 ones), 30 us at
+// 25 x 15 x 11 with every vector in global memory and the cells labelled on every
+// call; beyond 5120 cells, vectors in global memory, 47 us at 15625 (91 us before).
 //
 // A solve that ends without the tolerance returns the iterate of the smallest
 // residual.  Each step copies that iterate to global memory as it leaves it, a
@@ -115,7 +116,7 @@ __global__ __launch_bounds__(1024 / VJ) void k_bottom(Dims d, const T* __restric
     double rx[N], rv[N], rt[N];
     auto cell = [&](int u) { return tid + nt * u; };
     auto live = [&](int u) { return M == 0 || cell(u) < n; };
-    // f(u, u % 4) for every cell of this thread.  M > 0: the M slots without a
+    // f(u, u % VJ) for every cell of this thread.  M > 0: the M slots without a
     // branch (their LDS reads issue together); a slot past the last cell has
     // coefficients and vectors of 0, and its own place in LDS
     auto each = [&](auto f) {
@@ -404,9 +405,10 @@ void launch_bottom(const Dims& d, const T* rhs, T* phi, const T* cx, const T* cy
                            iters, skip_if_direct);
     };
     // three vectors of 5120 cells fill 120 of the 160 KB of LDS.  Threads by
-    // measurement (us per iteration at 280, 891, 3003 and 4125 cells): 256 give
-    // 2.2, 2.2, 7.6 and 13, 512 give 2.6, 2.1, 3.8 and 8.0, 1024 give 3.6, 2.9,
-    // 5.0 and 25 (coefficients spilt)
+    // measurement before the best iterate was copied out (us per iteration at 280,
+    // 891, 3003 and 4125 cells): 256 gave 2.2, 2.2, 7.6 and 13, 512 gave 2.6, 2.1,
+    // 3.8 and 8.0, 1024 gave 3.6, 2.9, 5.0 and 25 (coefficients spilt); the forms
+    // taken run at 2.3, 2.6, 4.1 and 7.1 now
     if (n <= 256) go(k_bottom<T, 4, 1>, 4);
     else if (n <= 512) go(k_bottom<T, 4, 2>, 4);
     else if (n <= 1024) go(k_bottom<T, 2, 2>, 2);

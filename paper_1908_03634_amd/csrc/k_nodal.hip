@@ -883,8 +883,9 @@ void launch_nd_correct(const NDims& d, double inv4h, const double* sg, const dou
 // LDS), and a sum takes one barrier.  1024 / VJ threads, sums in the association
 // of 1024; VJ = 0: the first wavefront alone, n <= 64, synchronised within it
 // (the other wavefronts of the workgroup wait at a later barrier), the same
-// bits.  336 nodes: 1.4 us per iteration, 4.2 us with the node coordinates, the
-// offsets and the sigmas found again in every pass.
+// bits.  336 nodes in a launch of its own: 1.4 us per iteration, 4.2 us with the
+// node coordinates, the offsets and the sigmas found again in every pass; inside
+// the coarse cycle, with 16 wavefronts at each barrier, about 2 us.
 template <typename T, int VJ, int M>
 __device__ void nd_cg(const NDims& d, const T* __restrict__ bin, T* __restrict__ xout, const T* __restrict__ sg,
                       double inv_h12, double rtol, int maxit, int use_x0, double* ps, double (*red)[2][kWaves],

@@ -227,10 +227,10 @@ enum { GS_PLAIN = 0, GS_ZERO = 1, GS_E_ALL = 2, GS_E_OWN = 3 };
 template <typename T>
 void launch_gs_blk(const Dims& d, T* x, const T* b, const T* cc, T h2, int colour, int mode, const T* ec,
                    double* phi, const double* irs, hipEvent_t ev0, hipEvent_t ev1, hipStream_t s);
-// Both colours of one red-black sweep in one pass, out of place (xo -> xn),
-// in FP32 when fsw_supported(d) (blocked layout, rows of at most 512 cells that
-// split into equal strips over a wavefront; whole rows per workgroup, rows
-// exchanged through LDS).  Modes:
+// Both colours of one red-black sweep in one pass, out of place (xo -> xn), in
+// FP32 when fsw_supported(d) and in FP64 when fsw64_supported(d) (blocked layout,
+// rows of at most 512 or 256 cells that split into equal strips over a wavefront;
+// whole rows per workgroup, rows exchanged through LDS).  Modes:
 //   FS_PLAIN:   xo as stored;
 //   FS_ZERO:    xo is zero (not read);
 //   FS_PROLONG: xo + e of each cell's parent coarse cell (ec), i.e. the
